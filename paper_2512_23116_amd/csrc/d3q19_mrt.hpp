@@ -1,13 +1,14 @@
 // d3q19_mrt.hpp — per-cell D3Q19 MRT-Smagorinsky-Guo collision for gfx950.
 //
-// One thread owns one cell.  The 19x19 moment transform of App. B
-// (eq. moment-matrix) is unrolled in registers: each opposite pair (2k, 2k+1)
-// contributes only its sum p_k to the even-parity rows (0, 1, 2, 9..15) and
-// only its difference d_k to the odd-parity rows (3..8, 16..18), so the forward
-// transform is ~95 additions and the inverse M^{-1} = M^T diag(1/n_r) mirrors
-// it.  Populations are deviations g = f - w rho0, whose moments are
-// M f - rho0 (1, -11, 3, 0, ..., 0); the equilibrium moments of eq. meq_fm are
-// printed in exactly that deviation form (row 0 is delta rho).
+// One thread owns one cell.  Populations are deviations g = f - w rho0, whose
+// moments are M f - rho0 (1, -11, 3, 0, ..., 0) (App. B eq. moment-matrix); the
+// equilibrium moments of eq. meq_fm are printed in exactly that deviation form
+// (row 0 is delta rho).  Two functions:
+//   cell_macro  density, velocity and tau_e of a cell (diagnostics);
+//   collide     the whole collision of the step kernels, in place.
+// Both split every opposite pair (2k, 2k+1) into its sum p_k, which alone
+// enters the even-parity rows (0, 1, 2, 9..15), and its difference d_k, which
+// alone enters the odd-parity rows (3..8, 16..18).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -40,20 +41,28 @@ __device__ __forceinline__ double fast_rcp(double x) { return 1.0 / x; }
 __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double fast_sqrt(double x) { return sqrt(x); }
 
-// Constants of one lattice's collision, in the arithmetic type R.
+// Constants of one lattice's collision, in the arithmetic type R.  Those that collide
+// reads come first, 96 bytes in FP32 (see LatticeArgs); cell_macro and the derivation
+// read the rest.
 template <typename R>
 struct CollideConst {
     R tau0;      // bare relaxation time
+    R rho0;
+    R tau0_sq;   // tau0^2
+    int32_t self_consistent;   // 1: s_9 = 1/tau_e in eq. yu_strain, closed form
+    // coefficients of collide, formed in FP64 by fill_collide_coefficients
+    R ea_sa, ea_sd, ea_r, ea_u2, ea_uF;   // even part of the axis pairs
+    R ed_sa, ed_sd, ed_r, ed_u2, ed_uF;   // even part of the diagonal pairs
+    R pi_m, pi_F;                         // rows 10 and 12: moment and force
+    R o_s, o_F;                           // odd part of the axis pairs
+    R a_j, a_s, a_F, a_m;                 // odd part of the diagonal pairs
+    R w_tr, c_tau;                        // tau_e - tau0 = c_tau sqrt(w), see collide
     R c3;        // 3 C (linear form) or 3 C^2; tau_e = tau0 + c3 |S|
     R a_e;       // s_e / (38 rho0): coefficient of m1_neq in S_aa (eq. yu_strain);
                  // 0 in the self-consistent mode
     R b9;        // s_9 / (2 rho0): coefficient of m9_neq in S_xx; s_9 = 1/tau0
                  // (explicit mode) or 1 (self-consistent mode: |S| = |S_1| / tau_e)
     R s_e, s_eps, s_q, s_pi, s_m;
-    R rho0;
-    R tau0_sq;   // tau0^2
-    int32_t self_consistent;   // 1: s_9 = 1/tau_e in eq. yu_strain, closed form
-    int32_t pad;
 };
 
 // Result of the macroscopic / closure half of the collision.
@@ -65,21 +74,74 @@ struct CellMacro {
     R snorm2;  // |S|^2 = 2 S:S of the strain that sets tau_e (diagnostics only)
 };
 
-// Collide one cell in place.  g: deviation populations (pre-collision in,
-// post-collision out).  F: body force at the cell.  kFull = false computes
-// only the macroscopic quantities and tau_e (diagnostics) and leaves g as is.
-//
-// kScaled: g and F come in units of 1/sigma (sigma g, sigma F, with sigma = 1/is
-// a power of two: the 16-bit storage scale) and g leaves in the same units, so
-// the storage codec needs no multiplications.  Every moment, equilibrium and
-// relaxed moment is then exactly sigma times its unscaled value (power-of-two
-// scaling commutes with rounding); the four places that need unscaled values
-// (rho, 1/rho, |S| -> tau_e, the diagnostics' |S|^2 and delta rho) apply is, so
-// the result equals sigma times the unscaled collision's, bit for bit.  The
-// returned CellMacro is unscaled either way.
-template <typename R, bool kFull, bool kScaled = false>
-__device__ __forceinline__ CellMacro<R> collide(R (&g)[19], R Fx, R Fy, R Fz,
-                                                const CollideConst<R>& k, R is = R(1)) {
+// The coefficients of collide from the rates already in k.  Every row of
+// eq. mrt_les_guo is m* = (1 - s) m + s m_eq + (1 - s/2) F_m, a linear form of the
+// pair sums and differences, the momentum, rho u u and u F; the rows with fixed
+// rates are folded here into one coefficient per input and output.
+inline void fill_collide_coefficients(CollideConst<double>& k) {
+    const double ge = 1.0 - 0.5 * k.s_e, geps = 1.0 - 0.5 * k.s_eps;
+    // t1 = m1*/2394, t2 = m2*/252 as forms of (sa, sd, r, rho u^2, u.F), with
+    // m1 = -11 sa + 8 sd - 30 r, m2 = -4 sa + sd + 12 r, t0 = (sa + sd + r)/19
+    const double t0 = 1.0 / 19.0;
+    const double t1[5] = {-11.0 / 2394.0, (8.0 - 19.0 * k.s_e) / 2394.0,
+                          (-30.0 + 19.0 * k.s_e) / 2394.0, 19.0 * k.s_e / 2394.0,
+                          38.0 * ge / 2394.0};
+    const double e2 = (1.0 - k.s_eps) / 252.0;
+    const double t2[5] = {-4.0 * e2, e2, 12.0 * e2, -475.0 / 63.0 * k.s_eps / 252.0,
+                          -11.0 * geps / 252.0};
+    double* ea[5] = {&k.ea_sa, &k.ea_sd, &k.ea_r, &k.ea_u2, &k.ea_uF};
+    double* ed[5] = {&k.ed_sa, &k.ed_sd, &k.ed_r, &k.ed_u2, &k.ed_uF};
+    for (int i = 0; i < 5; ++i) {
+        const double m = i < 3 ? t0 : 0.0;
+        *ea[i] = m - 11.0 * t1[i] - 4.0 * t2[i];
+        *ed[i] = m + 8.0 * t1[i] + t2[i];
+    }
+    k.pi_m = 1.0 - k.s_pi;
+    k.pi_F = -(1.0 - 0.5 * k.s_pi);
+    // odd rows: j* = rho u + F/2, q* of rows 4, 6, 8, and rows 16..18 through
+    // m16 - m17 = 4 d3 + d0 + d1 - jx - jy and its five counterparts, in terms of
+    // rho u_x, s0 = rho u_x - 3 d0 and F_x per axis
+    const double q = k.s_q, sm = (1.0 - k.s_m) / 8.0;
+    k.o_s = q / 6.0;
+    k.o_F = (2.0 - q) / 12.0;
+    k.a_j = k.s_m / 12.0;
+    k.a_s = ((1.0 - q) / 8.0 - sm) / 3.0;
+    k.a_F = ((1.0 + q) / 24.0 + sm) / 2.0;
+    k.a_m = 0.5 - 6.0 * k.a_j;
+    // |S|^2 = 6 (a_e n1)^2 + b9^2 (3 n9^2 + 9 n11^2 + 36 (n13^2 + n14^2 + n15^2)),
+    // n1 = 19 (sd - r - rho u^2)
+    k.w_tr = 2.0 * (19.0 * k.a_e / k.b9) * (19.0 * k.a_e / k.b9);
+    k.c_tau = k.c3 * k.b9 * 1.7320508075688772;
+}
+
+// The same constants in FP32 arithmetic: each rounded once from its FP64 value, but
+// for a_m.
+inline CollideConst<float> round_constants(const CollideConst<double>& k) {
+    CollideConst<float> f{};
+    f.tau0 = (float)k.tau0; f.c3 = (float)k.c3; f.a_e = (float)k.a_e; f.b9 = (float)k.b9;
+    f.s_e = (float)k.s_e; f.s_eps = (float)k.s_eps; f.s_q = (float)k.s_q;
+    f.s_pi = (float)k.s_pi; f.s_m = (float)k.s_m; f.rho0 = (float)k.rho0;
+    f.tau0_sq = (float)k.tau0_sq; f.self_consistent = k.self_consistent;
+    f.ea_sa = (float)k.ea_sa; f.ea_sd = (float)k.ea_sd; f.ea_r = (float)k.ea_r;
+    f.ea_u2 = (float)k.ea_u2; f.ea_uF = (float)k.ea_uF;
+    f.ed_sa = (float)k.ed_sa; f.ed_sd = (float)k.ed_sd; f.ed_r = (float)k.ed_r;
+    f.ed_u2 = (float)k.ed_u2; f.ed_uF = (float)k.ed_uF;
+    f.pi_m = (float)k.pi_m; f.pi_F = (float)k.pi_F;
+    f.o_s = (float)k.o_s; f.o_F = (float)k.o_F;
+    f.a_j = (float)k.a_j; f.a_s = (float)k.a_s; f.a_F = (float)k.a_F;
+    // exact in FP32 (a multiple of 2^-25 below 1/2), so that the momentum
+    // 2 o0 + 8 ax + 2 a_m (rho u_x - d0) keeps its rho u_x: a_m rounded on its own
+    // let it drift by up to 6e-8 a step
+    f.a_m = (float)(0.5 - 6.0 * (double)f.a_j);
+    f.w_tr = (float)k.w_tr; f.c_tau = (float)k.c_tau;
+    return f;
+}
+
+// Macroscopic quantities and tau_e of one cell (diagnostics).  g: deviation
+// populations, F: body force at the cell.
+template <typename R>
+__device__ __forceinline__ CellMacro<R> cell_macro(const R (&g)[19], R Fx, R Fy, R Fz,
+                                                   const CollideConst<R>& k) {
     const R h = R(0.5);
     // pair sums (even rows) and differences (odd rows)
     const R p0 = g[0] + g[1], d0 = g[0] - g[1];
@@ -98,31 +160,20 @@ __device__ __forceinline__ CellMacro<R> collide(R (&g)[19], R Fx, R Fy, R Fz,
     const R sd = (p3 + p4) + (p5 + p6) + (p7 + p8);  // diagonal pairs
     const R m0 = sa + sd + r;                  // delta rho
     const R m1 = R(-11) * sa + R(8) * sd - R(30) * r;
-    const R m2 = R(-4) * sa + sd + R(12) * r;
     const R jx = d0 + d3 + d4 + d7 + d8;
     const R jy = d1 + d3 - d4 + d5 + d6;
     const R jz = d2 + d5 - d6 + d7 - d8;
-    const R m4 = jx - R(5) * d0;
-    const R m6 = jy - R(5) * d1;
-    const R m8 = jz - R(5) * d2;
     const R v9 = (p3 + p4) + (p7 + p8) - R(2) * (p5 + p6);
     const R m9 = R(2) * p0 - p1 - p2 + v9;
-    const R m10 = R(-4) * p0 + R(2) * (p1 + p2) + v9;
     const R v11 = (p3 + p4) - (p7 + p8);
     const R m11 = p1 - p2 + v11;
-    const R m12 = R(2) * (p2 - p1) + v11;
     const R m13 = p3 - p4;
     const R m14 = p5 - p6;
     const R m15 = p7 - p8;
-    const R m16 = d3 + d4 - d7 - d8;
-    const R m17 = d4 - d3 + d5 + d6;
-    const R m18 = d6 - d5 + d7 - d8;
 
-    // eq. guo_velocity: rho u = sum f c + F/2 (rux.. and the products below carry
-    // the scale of g; u itself is unscaled)
-    const R drho = kScaled ? m0 * is : m0;
-    const R rho = k.rho0 + drho;
-    const R inv_rho = kScaled ? fast_rcp(rho) * is : fast_rcp(rho);
+    // eq. guo_velocity: rho u = sum f c + F/2
+    const R rho = k.rho0 + m0;
+    const R inv_rho = fast_rcp(rho);
     const R rux = jx + h * Fx, ruy = jy + h * Fy, ruz = jz + h * Fz;
     const R ux = rux * inv_rho, uy = ruy * inv_rho, uz = ruz * inv_rho;
     const R xx = rux * ux, yy = ruy * uy, zz = ruz * uz;   // rho u_a u_a
@@ -147,7 +198,7 @@ __device__ __forceinline__ CellMacro<R> collide(R (&g)[19], R Fx, R Fy, R Fz,
     const R S2 = R(2) * (Sxx * Sxx + Syy * Syy + Szz * Szz) +
                  R(4) * (Sxy * Sxy + Sxz * Sxz + Syz * Syz);
     // eq. les_viscosity: tau_e = 1/2 + 3 (nu0 + C Delta^2 |S|) = tau0 + 3 C |S|
-    R tau_t = (kScaled ? k.c3 * is : k.c3) * fast_sqrt(S2);
+    R tau_t = k.c3 * fast_sqrt(S2);
     if (k.self_consistent) {
         // (the empty asm keeps this a uniform branch instead of computing it
         // always and selecting, so the default mode pays nothing for it)
@@ -159,83 +210,142 @@ __device__ __forceinline__ CellMacro<R> collide(R (&g)[19], R Fx, R Fy, R Fz,
         tau_t = R(2) * tau_t * fast_rcp(k.tau0 + fast_sqrt(k.tau0_sq + R(4) * tau_t));
     }
     const R tau_e = k.tau0 + tau_t;
-    // |S|^2: S2 itself, or (|S_1| / tau_e)^2 in the self-consistent mode.  Only the
-    // diagnostics read it; the step kernels drop it.
-    const R S2u = kScaled ? S2 * (is * is) : S2;
-    const R snorm2 = k.self_consistent ? S2u * fast_rcp(tau_e * tau_e) : S2u;
+    // |S|^2: S2 itself, or (|S_1| / tau_e)^2 in the self-consistent mode
+    const R snorm2 = k.self_consistent ? S2 * fast_rcp(tau_e * tau_e) : S2;
+    return CellMacro<R>{m0, rho, ux, uy, uz, tau_t, snorm2};
+}
 
-    CellMacro<R> out{drho, rho, ux, uy, uz, tau_t, snorm2};
-    if constexpr (!kFull) {
-        return out;
-    } else {
-        const R s_nu = fast_rcp(tau_e);
-        // eq. meq_fm: force moments
-        const R X = ux * Fx, Y = uy * Fy, Z = uz * Fz;
-        const R uF = X + Y + Z;
-        const R P = R(2) * X - Y - Z;
-        const R Qw = Y - Z;
-        const R third2 = R(2) / R(3);
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-        // eq. mrt_les_guo in moment space: m* = m - S (m - m_eq) + (I - S/2) F_m,
-        // each row pre-divided by its norm n_r = (M M^T)_rr
-        const R ge = R(1) - h * k.s_e, geps = R(1) - h * k.s_eps, gq = R(1) - h * k.s_q;
-        const R gpi = R(1) - h * k.s_pi, gnu = R(1) - h * s_nu;
-        const R t0 = m0 * R(1.0 / 19.0);
-        const R t1 = (m1 - k.s_e * n1 + ge * R(38) * uF) * R(1.0 / 2394.0);
-        const R t2 = (m2 - k.s_eps * (m2 + R(475.0 / 63.0) * ru2) + geps * R(-11) * uF) *
-                     R(1.0 / 252.0);
-        const R t3 = (rux + h * Fx) * R(0.1);
-        const R t5 = (ruy + h * Fy) * R(0.1);
-        const R t7 = (ruz + h * Fz) * R(0.1);
-        const R t4 = (m4 - k.s_q * (m4 + third2 * rux) - gq * third2 * Fx) * R(1.0 / 40.0);
-        const R t6 = (m6 - k.s_q * (m6 + third2 * ruy) - gq * third2 * Fy) * R(1.0 / 40.0);
-        const R t8 = (m8 - k.s_q * (m8 + third2 * ruz) - gq * third2 * Fz) * R(1.0 / 40.0);
-        const R t9 = (m9 - s_nu * n9 + gnu * R(2) * P) * R(1.0 / 36.0);
-        const R t10 = ((R(1) - k.s_pi) * m10 - gpi * P) * R(1.0 / 72.0);
-        const R t11 = (m11 - s_nu * n11 + gnu * R(2) * Qw) * R(1.0 / 12.0);
-        const R t12 = ((R(1) - k.s_pi) * m12 - gpi * Qw) * R(1.0 / 24.0);
-        const R t13 = (m13 - s_nu * n13 + gnu * (ux * Fy + uy * Fx)) * R(0.25);
-        const R t14 = (m14 - s_nu * n14 + gnu * (uy * Fz + uz * Fy)) * R(0.25);
-        const R t15 = (m15 - s_nu * n15 + gnu * (ux * Fz + uz * Fx)) * R(0.25);
-        const R sm = (R(1) - k.s_m) * R(0.125);
-        const R t16 = sm * m16, t17 = sm * m17, t18 = sm * m18;
+// Collide one cell in place (eq. mrt_les_guo).  g: deviation populations
+// (pre-collision in, post-collision out).  F: body force at the cell.
+//
+// The two-step and the 16-bit kernels are bound by VALU issue (and the rest run
+// with 25-36 % of it busy), so the moments are never formed one by one: rows with
+// a fixed rate are linear forms whose coefficients the host folds
+// (fill_collide_coefficients), and only the five shear rows, whose rate differs
+// per cell, are relaxed as moments.  With A = p3 + p4, B = p5 + p6, C = p7 + p8:
+//   axis pairs, even:     ea +- ..., ea = forms of (sa, sd, r, rho u^2, u.F)
+//   diagonal pairs, even: ed +- ...
+//   rows 9 / 10:  m9 = a + b, m10 = b - 2 a,  a = 3 p0 - sa, b = sd - 3 B
+//   rows 11 / 12: m11 = c + d, m12 = d - 2 c, c = p1 - p2,   d = A - C
+//   odd parts:    o0 and ax, forms of rho u_x, s = rho u_x - 3 d0 and F_x per axis;
+//                 a_m d_k plus the sum or difference of two axes' ax per diagonal pair
+// and |S|^2 needs n1 = 19 (sd - r - rho u^2), n9, n11, n13..15 squared only.  That is
+// 208 floating-point instructions per cell where the row-by-row form took 288.  The
+// rest population is what mass leaves after the others, so that the rounding of the
+// coefficients cannot drift it (for momentum see round_constants).
+// Every product-sum is an explicit fused multiply-add and contraction is off, so
+// all kernels that inline this give the same bits.
+//
+// kScaled: g and F come in units of 1/sigma (sigma g, sigma F, with sigma = 1/is
+// a power of two: the 16-bit storage scale) and g leaves in the same units, so
+// the storage codec needs no multiplications.  Every intermediate is then exactly
+// sigma times its unscaled value (power-of-two scaling commutes with rounding);
+// the places that need unscaled values (rho, 1/rho, tau_e) apply is, so the result
+// equals sigma times the unscaled collision's, bit for bit.
+template <typename R, bool kScaled = false>
+__device__ __forceinline__ void collide(R (&g)[19], R Fx, R Fy, R Fz, const CollideConst<R>& k,
+                                        R is = R(1)) {
+#pragma clang fp contract(off)
+    const R p0 = g[0] + g[1], d0 = g[0] - g[1];
+    const R p1 = g[2] + g[3], d1 = g[2] - g[3];
+    const R p2 = g[4] + g[5], d2 = g[4] - g[5];
+    const R p3 = g[6] + g[7], d3 = g[6] - g[7];
+    const R p4 = g[8] + g[9], d4 = g[8] - g[9];
+    const R p5 = g[10] + g[11], d5 = g[10] - g[11];
+    const R p6 = g[12] + g[13], d6 = g[12] - g[13];
+    const R p7 = g[14] + g[15], d7 = g[14] - g[15];
+    const R p8 = g[16] + g[17], d8 = g[16] - g[17];
+    const R r = g[18];
+    const R A = p3 + p4, B = p5 + p6, C = p7 + p8;
+    const R sa = p0 + (p1 + p2), sd = B + (A + C);
+    const R m0 = r + (sa + sd);                  // delta rho
 
-        // g* = M^T (m* / n): even part E_k, odd part O_k per pair
-        const R ea = t0 - R(11) * t1 - R(4) * t2;
-        const R e0 = ea + R(2) * t9 - R(4) * t10;
-        const R eyz = ea - t9 + R(2) * t10;
-        const R e1 = eyz + t11 - R(2) * t12;
-        const R e2 = eyz - t11 + R(2) * t12;
-        const R o0 = t3 - R(4) * t4;
-        const R o1 = t5 - R(4) * t6;
-        const R o2 = t7 - R(4) * t8;
-        const R ed = t0 + R(8) * t1 + t2;
-        const R exy = ed + t9 + t10 + t11 + t12;
-        const R eyz2 = ed - R(2) * (t9 + t10);
-        const R exz = ed + t9 + t10 - t11 - t12;
-        const R e3 = exy + t13, e4 = exy - t13;
-        const R e5 = eyz2 + t14, e6 = eyz2 - t14;
-        const R e7 = exz + t15, e8 = exz - t15;
-        const R ax = t3 + t4, ay = t5 + t6, az = t7 + t8;
-        const R o3 = ax + ay + t16 - t17;
-        const R o4 = ax - ay + t16 + t17;
-        const R o5 = ay + az + t17 - t18;
-        const R o6 = ay - az + t17 + t18;
-        const R o7 = ax + az - t16 + t18;
-        const R o8 = ax - az - t16 - t18;
+    // eq. guo_velocity: rho u = sum f c + F/2 (rux.. and the products below carry
+    // the scale of g; u itself is unscaled)
+    const R rux = mad(R(0.5), Fx, d0 + ((d3 + d4) + (d7 + d8)));
+    const R ruy = mad(R(0.5), Fy, d1 + ((d3 - d4) + (d5 + d6)));
+    const R ruz = mad(R(0.5), Fz, d2 + ((d5 - d6) + (d7 - d8)));
+    const R rho = kScaled ? mad(m0, is, k.rho0) : k.rho0 + m0;
+    const R inv_rho = kScaled ? fast_rcp(rho) * is : fast_rcp(rho);
+    const R ux = rux * inv_rho, uy = ruy * inv_rho, uz = ruz * inv_rho;
+    const R xx = rux * ux, zz = ruz * uz;      // rho u_a u_a
+    const R yz = mad(ruy, uy, zz), y_z = mad(ruy, uy, -zz);
+    const R ru2 = xx + yz;
+    const R XF = ux * Fx, ZF = uz * Fz;        // u_a F_a
+    const R YZ = mad(uy, Fy, ZF), Y_Z = mad(uy, Fy, -ZF);
+    const R uF = XF + YZ;
+    const R PF = mad(R(2), XF, -YZ);           // 2 u_x F_x - u_y F_y - u_z F_z
+    const R Fxy = mad(ux, Fy, uy * Fx), Fyz = mad(uy, Fz, uz * Fy), Fxz = mad(ux, Fz, uz * Fx);
 
-        g[0] = e0 + o0;  g[1] = e0 - o0;
-        g[2] = e1 + o1;  g[3] = e1 - o1;
-        g[4] = e2 + o2;  g[5] = e2 - o2;
-        g[6] = e3 + o3;  g[7] = e3 - o3;
-        g[8] = e4 + o4;  g[9] = e4 - o4;
-        g[10] = e5 + o5; g[11] = e5 - o5;
-        g[12] = e6 + o6; g[13] = e6 - o6;
-        g[14] = e7 + o7; g[15] = e7 - o7;
-        g[16] = e8 + o8; g[17] = e8 - o8;
-        g[18] = t0 - R(30) * t1 + R(12) * t2;
-        return out;
+    // shear rows and the trace: moments and their non-equilibrium parts (eq. meq_fm)
+    const R a = mad(R(3), p0, -sa), b = mad(R(-3), B, sd);
+    const R c = p1 - p2, d = A - C;
+    const R m9 = a + b, m11 = c + d, m13 = p3 - p4, m14 = p5 - p6, m15 = p7 - p8;
+    const R n1 = sd - r - ru2;
+    const R n9 = m9 - mad(R(2), xx, -yz), n11 = m11 - y_z;
+    const R n13 = mad(-rux, uy, m13), n14 = mad(-ruy, uz, m14), n15 = mad(-rux, uz, m15);
+
+    // eq. yu_strain, eq. strain_norm, eq. les_viscosity: tau_e = tau0 + c_tau sqrt(w)
+    const R off = mad(n13, n13, mad(n14, n14, n15 * n15));
+    const R w = mad(k.w_tr, n1 * n1, mad(R(12), off, mad(R(3), n11 * n11, n9 * n9)));
+    R tau_t = (kScaled ? k.c_tau * is : k.c_tau) * fast_sqrt(w);
+    if (k.self_consistent) {
+        // (the empty asm keeps this a uniform branch instead of computing it
+        // always and selecting, so the default mode pays nothing for it)
+        asm volatile("");
+        // the positive root of tau_e^2 - tau0 tau_e - c3 |S_1| = 0 as its
+        // increment over tau0, as in cell_macro
+        tau_t = R(2) * tau_t * fast_rcp(k.tau0 + fast_sqrt(mad(R(4), tau_t, k.tau0_sq)));
     }
+    const R s = -fast_rcp(k.tau0 + tau_t);     // -s_nu
+
+    // relaxed shear rows m + F_m - s_nu (m - m_eq + F_m / 2), rows 10 and 12
+    const R q9 = mad(s, n9 + PF, mad(R(2), PF, m9));
+    const R q10 = mad(k.pi_F, PF, k.pi_m * mad(R(-2), a, b));
+    const R q11 = mad(s, n11 + Y_Z, mad(R(2), Y_Z, m11));
+    const R q12 = mad(k.pi_F, Y_Z, k.pi_m * mad(R(-2), c, d));
+    const R q13 = mad(s, mad(R(0.5), Fxy, n13), m13 + Fxy);
+    const R q14 = mad(s, mad(R(0.5), Fyz, n14), m14 + Fyz);
+    const R q15 = mad(s, mad(R(0.5), Fxz, n15), m15 + Fxz);
+
+    // g* = M^-1 m*: even part per pair
+    const R ea = mad(k.ea_uF, uF, mad(k.ea_u2, ru2, mad(k.ea_r, r, mad(k.ea_sd, sd, k.ea_sa * sa))));
+    const R ed = mad(k.ed_uF, uF, mad(k.ed_u2, ru2, mad(k.ed_r, r, mad(k.ed_sd, sd, k.ed_sa * sa))));
+    const R D9 = q9 - q10, D11 = q11 - q12;
+    const R Q9 = mad(R(2), q9, q10), Q11 = mad(R(2), q11, q12);
+    const R e0 = mad(R(1.0 / 18.0), D9, ea), ey = mad(R(-1.0 / 36.0), D9, ea);
+    const R e1 = mad(R(1.0 / 12.0), D11, ey), e2 = mad(R(-1.0 / 12.0), D11, ey);
+    const R ex = mad(R(1.0 / 72.0), Q9, ed), eyz = mad(R(-1.0 / 36.0), Q9, ed);
+    const R exy = mad(R(1.0 / 24.0), Q11, ex), exz = mad(R(-1.0 / 24.0), Q11, ex);
+    const R e3 = mad(R(0.25), q13, exy), e4 = mad(R(-0.25), q13, exy);
+    const R e5 = mad(R(0.25), q14, eyz), e6 = mad(R(-0.25), q14, eyz);
+    const R e7 = mad(R(0.25), q15, exz), e8 = mad(R(-0.25), q15, exz);
+    // odd part per pair, as the old one plus what its departure from equilibrium
+    // (s = 0) and the force change: what is rounded is small
+    const R sx = mad(R(-3), d0, rux), sy = mad(R(-3), d1, ruy), sz = mad(R(-3), d2, ruz);
+    const R o0 = mad(R(0.5), d0, mad(k.o_F, Fx, k.o_s * sx));
+    const R o1 = mad(R(0.5), d1, mad(k.o_F, Fy, k.o_s * sy));
+    const R o2 = mad(R(0.5), d2, mad(k.o_F, Fz, k.o_s * sz));
+    const R ax = mad(k.a_j, rux, mad(k.a_F, Fx, k.a_s * sx));
+    const R ay = mad(k.a_j, ruy, mad(k.a_F, Fy, k.a_s * sy));
+    const R az = mad(k.a_j, ruz, mad(k.a_F, Fz, k.a_s * sz));
+    const R o3 = mad(k.a_m, d3, ax + ay), o4 = mad(k.a_m, d4, ax - ay);
+    const R o5 = mad(k.a_m, d5, ay + az), o6 = mad(k.a_m, d6, ay - az);
+    const R o7 = mad(k.a_m, d7, ax + az), o8 = mad(k.a_m, d8, ax - az);
+
+    g[0] = e0 + o0;  g[1] = e0 - o0;
+    g[2] = e1 + o1;  g[3] = e1 - o1;
+    g[4] = e2 + o2;  g[5] = e2 - o2;
+    g[6] = e3 + o3;  g[7] = e3 - o3;
+    g[8] = e4 + o4;  g[9] = e4 - o4;
+    g[10] = e5 + o5; g[11] = e5 - o5;
+    g[12] = e6 + o6; g[13] = e6 - o6;
+    g[14] = e7 + o7; g[15] = e7 - o7;
+    g[16] = e8 + o8; g[17] = e8 - o8;
+    g[18] = mad(R(-12), ed, mad(R(-6), ea, m0));   // mass: m0 = 6 ea + 12 ed + g18
 }
 
 }  // namespace lbm

@@ -379,15 +379,11 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_handle** out) {
     kd.b9 = (sc ? 1.0 : 1.0 / cfg->tau0) / (2.0 * cfg->rho0);
     kd.tau0_sq = cfg->tau0 * cfg->tau0;
     kd.self_consistent = sc ? 1 : 0;
-    kd.pad = 0;
     kd.s_e = cfg->s_e; kd.s_eps = cfg->s_eps; kd.s_q = cfg->s_q; kd.s_pi = cfg->s_pi;
     kd.s_m = cfg->s_m;
     kd.rho0 = cfg->rho0;
-    CollideConst<float>& kf = a.kf;
-    kf.tau0 = (float)kd.tau0; kf.c3 = (float)kd.c3; kf.a_e = (float)kd.a_e; kf.b9 = (float)kd.b9;
-    kf.s_e = (float)kd.s_e; kf.s_eps = (float)kd.s_eps; kf.s_q = (float)kd.s_q;
-    kf.s_pi = (float)kd.s_pi; kf.s_m = (float)kd.s_m; kf.rho0 = (float)kd.rho0;
-    kf.tau0_sq = (float)kd.tau0_sq; kf.self_consistent = kd.self_consistent; kf.pad = 0;
+    fill_collide_coefficients(kd);
+    a.kf = round_constants(kd);
     a.tau0 = cfg->tau0;
     a.rho0 = cfg->rho0;
     a.sigma = h->cfg.storage_scale;

@@ -30,12 +30,10 @@ __device__ __forceinline__ uint16_t bf16_rne(float x) {
 }
 
 // Whether the one-step kernel collides on the stored scale (collide's kScaled),
-// so that the codec reduces to conversions: for BF16 (shift / convert plus a
-// multiply each way otherwise).  FP16 keeps the unscaled form: its decode and
-// encode already fold the scale into mixed-precision FMAs (v_fma_mix*), and
-// the scaled form measured 5 VALU instructions more per cell.
+// so that the 16-bit codecs reduce to conversions instead of a conversion and a
+// multiplication each way (FP16: 19 VALU instructions per cell fewer).
 template <class Cd>
-constexpr bool kScaledCodec = std::is_same_v<Cd, CdBF16>;
+constexpr bool kScaledCodec = sizeof(typename Cd::T) == 2;
 
 template <class Cd>
 __device__ __forceinline__ typename Cd::R dec(typename Cd::T v, typename Cd::R inv_s) {
@@ -120,9 +118,10 @@ __device__ __forceinline__ uint64_t canon_index(int pat, int i, uint32_t cell, c
     return (uint64_t)slot * plane + c;
 }
 
-// Block of cells of this workgroup in the XCD-aware order of L.xcd_remap.
+// Block of cells of this workgroup in the XCD-aware order of L.xcd_remap, for a launch
+// of one block per 256 cells (counted here: gridDim would be one more scalar load).
 __device__ __forceinline__ uint32_t block_id(const LatticeArgs& L) {
-    return block_order(blockIdx.x, gridDim.x, L.xcd_remap);
+    return block_order(blockIdx.x, (L.ncell + 255u) / 256u, L.xcd_remap);
 }
 
 // Plane addressing.  The 64-bit base of plane `slot` is uniform (SGPRs) and
@@ -134,21 +133,33 @@ __device__ __forceinline__ uint32_t block_id(const LatticeArgs& L) {
 //    a loop);
 //  * PlaneStride: array base + slot * plane bytes (a few scalar instructions,
 //    no extra SGPRs held; used by the z-marching two-step kernel).
+// Both return pointers of the global address space, so that the accesses are
+// global_load / global_store with a scalar base also where the compiler cannot see
+// where the base comes from (the two-step kernel hides it; a generic pointer there
+// costs a flat access and a 64-bit vector addition each).
+#if defined(__HIP_DEVICE_COMPILE__)
+#define LBM_GLOBAL_SPACE __attribute__((address_space(1)))
+#else
+#define LBM_GLOBAL_SPACE
+#endif
 struct PlaneTable {
     char* const* p;
-    __device__ __forceinline__ char* operator()(int slot) const { return p[slot]; }
+    __device__ __forceinline__ LBM_GLOBAL_SPACE char* operator()(int slot) const {
+        return (LBM_GLOBAL_SPACE char*)p[slot];
+    }
 };
 struct PlaneStride {
     char* base;
     uint64_t bytes;
-    __device__ __forceinline__ char* operator()(int slot) const {
-        return base + (uint64_t)slot * bytes;
+    __device__ __forceinline__ LBM_GLOBAL_SPACE char* operator()(int slot) const {
+        return (LBM_GLOBAL_SPACE char*)(base + (uint64_t)slot * bytes);
     }
 };
 
 template <typename T, class Planes>
-__device__ __forceinline__ T* elem_ptr(const Planes& planes, int slot, uint32_t c) {
-    return (T*)(planes(slot) + (uint32_t)(c * (uint32_t)sizeof(T)));
+__device__ __forceinline__ LBM_GLOBAL_SPACE T* elem_ptr(const Planes& planes, int slot,
+                                                        uint32_t c) {
+    return (LBM_GLOBAL_SPACE T*)(planes(slot) + (uint32_t)(c * (uint32_t)sizeof(T)));
 }
 
 // Location of the pre-collision f_i(x) for pattern PAT: slot and cell.
@@ -161,7 +172,7 @@ __device__ __forceinline__ void load_cell(const Planes& planes, uint32_t cell,
         constexpr int i = decltype(I)::value;
         constexpr int slot = (PAT == PAT_AA_ODD) ? opp_of(i) : i;
         const uint32_t c = (PAT == PAT_AA_EVEN) ? cell : cell + (uint32_t)off_minus<i>(nb);
-        const typename Cd::T* p = elem_ptr<const typename Cd::T>(planes, slot, c);
+        LBM_GLOBAL_SPACE const typename Cd::T* p = elem_ptr<const typename Cd::T>(planes, slot, c);
         if constexpr (kNT) g[i] = dec<Cd>(__builtin_nontemporal_load(p), inv_s);
         else g[i] = dec<Cd>(*p, inv_s);
     });
@@ -177,7 +188,7 @@ __device__ __forceinline__ void store_cell(const Planes& planes, uint32_t cell,
         constexpr int i = decltype(I)::value;
         constexpr int slot = (PAT == PAT_AA_EVEN) ? opp_of(i) : i;
         const uint32_t c = (PAT == PAT_AA_ODD) ? cell + (uint32_t)off_minus<opp_of(i)>(nb) : cell;
-        typename Cd::T* p = elem_ptr<typename Cd::T>(planes, slot, c);
+        LBM_GLOBAL_SPACE typename Cd::T* p = elem_ptr<typename Cd::T>(planes, slot, c);
         if constexpr (kNT) __builtin_nontemporal_store(enc<Cd>(g[i], s), p);
         else *p = enc<Cd>(g[i], s);
     });
@@ -216,6 +227,23 @@ __device__ __forceinline__ void force_at(const LatticeArgs& L, const CellPos& p,
     Fz = rc[2] + s1 * rc[5] + c1 * rc[8] + s2 * rc[11] + c2 * rc[14];
 }
 
+// The collision's constants, read before the populations are waited for.  Left where
+// they are first used, their scalar loads come after that wait and add to it: the
+// 100^3 FP32 A/B step then takes 24.1 us instead of 23.7, 129x127x130 AA 48.8
+// instead of 48.3.  (FP64 has the registers for neither; see k_step.)
+__device__ __forceinline__ CollideConst<float> early(const CollideConst<float>& c) {
+    CollideConst<float> k = c;
+    asm volatile("" : "+s"(k.ea_sa), "+s"(k.ea_sd), "+s"(k.ea_r), "+s"(k.ea_u2), "+s"(k.ea_uF),
+                      "+s"(k.ed_sa), "+s"(k.ed_sd), "+s"(k.ed_r), "+s"(k.ed_u2), "+s"(k.ed_uF));
+    asm volatile("" : "+s"(k.pi_m), "+s"(k.pi_F), "+s"(k.o_s), "+s"(k.o_F), "+s"(k.a_j),
+                      "+s"(k.a_s), "+s"(k.a_F), "+s"(k.a_m), "+s"(k.w_tr), "+s"(k.c_tau),
+                      "+s"(k.tau0), "+s"(k.rho0));
+    return k;
+}
+__device__ __forceinline__ const CollideConst<double>& early(const CollideConst<double>& c) {
+    return c;
+}
+
 // One cell of the fused stream-and-collide step (eq. mrt_les_guo): gather the
 // 19 pre-collision populations of pattern PAT, collide, scatter.
 // NT: bit 0 = non-temporal loads, bit 1 = non-temporal stores.
@@ -225,6 +253,7 @@ __device__ __forceinline__ void step_cell(const LatticeArgs& L, uint32_t cell) {
     const CellPos p = decode(cell, L);
     const Nbr nb = make_nbr(p, L);
     constexpr bool kS = kScaledCodec<Cd>;
+    const auto& k = early(collide_const<R>(L));
     R g[19];
     load_cell<Cd, PAT, (NT & 1) != 0>(PlaneTable{L.pa}, cell, nb, g,
                                       kS ? R(1) : inv_scale_of<R>(L));
@@ -236,7 +265,7 @@ __device__ __forceinline__ void step_cell(const LatticeArgs& L, uint32_t cell) {
         Fy *= s;
         Fz *= s;
     }
-    collide<R, true, kS>(g, Fx, Fy, Fz, collide_const<R>(L), inv_scale_of<R>(L));
+    collide<R, kS>(g, Fx, Fy, Fz, k, inv_scale_of<R>(L));
     // Rebuild the store addresses from here: an empty register barrier on the
     // cell index keeps the compiler from holding 19 precomputed 64-bit store
     // addresses live across the collision (38 VGPRs), so stores use the same

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <string>
@@ -21,29 +22,33 @@ namespace lbm {
 //   AB     : f_i(x) is at slot i of cell x-c_i in the current array
 enum Pattern : int { PAT_AA_EVEN = 0, PAT_AA_ODD = 1, PAT_AB = 2 };
 
-// Everything a kernel needs about one lattice, passed by value.
+// Everything a kernel needs about one lattice, passed by value.  What the FP32 and
+// 16-bit step kernels read comes first, packed into as few 64-byte lines as it fits:
+// every launch finds the scalar cache cold, and each further line is a miss that all
+// its first waves wait for (0.2 us of a 24 us launch at 100^3).
 struct LatticeArgs {
-    void* a;                 // population array (AA: the only one; AB: current source)
-    void* b;                 // AB: destination; AA: == a
-    uint64_t plane;          // elements per direction plane (padded); plane bytes < 2^32
-    char* pa[19];            // plane i of a: a + i * plane * element bytes
-    char* pb[19];            // plane i of b (precomputed on the host: kernels take the
-                             // 64-bit plane bases from kernel arguments, no scalar math)
     uint32_t nx, ny, nz, nxy, ncell;
+    int32_t xcd_remap;       // step-kernel block order: 0 dispatch order, 1 one contiguous
+                             // range per XCD, K >= 2 chunks of K blocks in turn
     DivMagic mx, my;         // division by nx (cell -> row) and ny (row -> z)
     const void* rowc;        // force row coefficients [ny*nz][16] in R, or null
     const void* xtab;        // [nx][4] sin/cos of the first two x harmonics, in R
+    float sigma_f, inv_sigma_f;   // FP16/BF16 storage scale
+    CollideConst<float> kf;  // collision constants, rounded to FP32 on the host
+    char* pa[19];            // plane i of a: a + i * plane * element bytes
+    char* pb[19];            // plane i of b (precomputed on the host: kernels take the
+                             // 64-bit plane bases from kernel arguments, no scalar math)
+    void* a;                 // population array (AA: the only one; AB: current source)
+    void* b;                 // AB: destination; AA: == a
+    uint64_t plane;          // elements per direction plane (padded); plane bytes < 2^32
     CollideConst<double> kd; // collision constants for FP64 arithmetic
-    CollideConst<float> kf;  // the same rounded to FP32 on the host
     double tau0, rho0;
     double sigma, inv_sigma; // FP16/BF16 storage scale
-    float sigma_f, inv_sigma_f;
-    int32_t xcd_remap;       // step-kernel block order: 0 dispatch order, 1 one contiguous
-                             // range per XCD, K >= 2 chunks of K blocks in turn
     int32_t nt_mode;         // step kernel: bit 1 non-temporal stores
     uint32_t elem_bytes;     // bytes per stored population
-    uint32_t pad_;
 };
+static_assert(offsetof(LatticeArgs, kf) == 64 && offsetof(CollideConst<float>, c3) == 96,
+              "step arguments fill their cache lines");
 
 // Kernel launchers (lbm_kernels.hip).  All return the launch status.
 hipError_t launch_tables(int precision, const LatticeArgs& L, const lbm_force_mode* d_modes,

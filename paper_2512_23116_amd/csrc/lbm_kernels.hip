@@ -19,8 +19,14 @@
 namespace lbm {
 
 // ------------------------------------------------------------ the step ---
+// FP64 takes 96-104 VGPRs; held to 4 waves per SIMD, as its 108-114 had been, it runs
+// at 968 us on 256^3 A/B against 981 with the 5 that 96 allow (more waves than its
+// 8-byte streams gain from).  The rest run 8.
 template <class Cd, int PAT, int NT>
-__global__ __launch_bounds__(256) void k_step(LatticeArgs L) {
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(std::is_same_v<Cd, CdF64> ? 4 : 1,
+                                   std::is_same_v<Cd, CdF64> ? 4 : 8)))
+void k_step(LatticeArgs L) {
     const uint32_t cell = block_id(L) * 256u + threadIdx.x;
     if (cell >= L.ncell) return;
     step_cell<Cd, PAT, NT>(L, cell);
@@ -86,7 +92,7 @@ __global__ __launch_bounds__(256) void k_diag(LatticeArgs L, double* partials) {
         for (int i = 0; i < 19; ++i) finite = finite && isfinite(g[i]);
         R Fx, Fy, Fz;
         force_at<R>(L, p, Fx, Fy, Fz);
-        const CellMacro<R> m = collide<R, false>(g, Fx, Fy, Fz, k);
+        const CellMacro<R> m = cell_macro<R>(g, Fx, Fy, Fz, k);
         const double tt = (double)m.tau_t;   // tau_e - tau0 = c3 |S| >= 0
         finite = finite && isfinite(tt);
         if (!finite) {
@@ -164,7 +170,7 @@ __global__ __launch_bounds__(256) void k_moments(LatticeArgs L, double* rho, dou
     load_cell<Cd, PAT>(PlaneTable{L.pa}, cell, nb, g, inv_scale_of<R>(L));
     R Fx, Fy, Fz;
     force_at<R>(L, p, Fx, Fy, Fz);
-    const CellMacro<R> m = collide<R, false>(g, Fx, Fy, Fz, collide_const<R>(L));
+    const CellMacro<R> m = cell_macro<R>(g, Fx, Fy, Fz, collide_const<R>(L));
     if (rho) rho[cell] = L.rho0 + (double)m.drho;
     if (u) {
         u[cell] = (double)m.ux;
@@ -185,7 +191,7 @@ __device__ __forceinline__ double cell_theta(const LatticeArgs& L, uint32_t cell
     load_cell<Cd, PAT>(PlaneTable{L.pa}, cell, nb, g, inv_scale_of<R>(L));
     R Fx, Fy, Fz;
     force_at<R>(L, p, Fx, Fy, Fz);
-    const CellMacro<R> m = collide<R, false>(g, Fx, Fy, Fz, collide_const<R>(L));
+    const CellMacro<R> m = cell_macro<R>(g, Fx, Fy, Fz, collide_const<R>(L));
     return (L.tau0 - 0.5) + (double)m.tau_t;
 }
 

@@ -13,10 +13,16 @@
 
 namespace lbm {
 
-// Extended tile of one workgroup: 64 x 16 columns, of which the inner 62 x 14
-// are the tile and the rest its one-cell halo.
-constexpr int TB_EX = 64, TB_TX = TB_EX - 2;
-constexpr int kTbEY = 16, kTbTY = kTbEY - 2;
+// Tile of one workgroup, extended by a one-cell halo, in one of two shapes: 64 x 13
+// columns with the halo columns in a wave of their own, or 62 x 14 (64 x 16 with the
+// halo) in a wave per row.  lbm_tb2.hip says which lattice takes which, and why.
+template <bool kWave>
+struct Tb2Tile {
+    static constexpr int TX = kWave ? 64 : 62, TY = kWave ? 13 : 14;
+    static constexpr int EX = TX + 2, EY = TY + 2;
+    static constexpr int kThreads = 64 * (EY + (kWave ? 1 : 0));
+};
+constexpr int TB_TX = Tb2Tile<true>::TX, kTbTY = Tb2Tile<true>::TY;
 constexpr int TB_MAX_CHUNKS = 64;
 
 // Work plan of a launch: the tiles are split into `groups` contiguous ranges
@@ -50,14 +56,15 @@ struct Tb2Plan {
     uint32_t per_group = 0;   // workgroups per group: the launch has groups * per_group
 };
 
-// Relative cost of one plane of a tile: phase 1 runs on all 64 x 16 columns,
-// phase 2 on the interior only, about 35 % of a full tile's time (a tile with
-// 2 of its 14 interior rows takes 0.70 of a full one at 800^3).
-inline double tile_cost(uint32_t tile, uint32_t tiles_x, uint32_t nx, uint32_t ny) {
+// Relative cost of one plane of a tile: phase 1 runs on all its columns,
+// phase 2 on the interior only, about 35 % of a full tile's time (a 62 x 14
+// tile with 2 of its 14 interior rows takes 0.70 of a full one at 800^3).
+inline double tile_cost(uint32_t tile, uint32_t tiles_x, uint32_t nx, uint32_t ny,
+                        uint32_t tw, uint32_t th) {
     const uint32_t x = tile % tiles_x, y = tile / tiles_x;
-    const uint32_t w = std::min<uint32_t>(TB_TX, nx - x * TB_TX);
-    const uint32_t h = std::min<uint32_t>(kTbTY, ny - y * kTbTY);
-    return 0.65 + 0.35 * double(w * h) / double(TB_TX * kTbTY);
+    const uint32_t w = std::min<uint32_t>(tw, nx - x * tw);
+    const uint32_t h = std::min<uint32_t>(th, ny - y * th);
+    return 0.65 + 0.35 * double(w * h) / double(tw * th);
 }
 
 // Finishing time of the slowest group when each group's CUs take its items in
@@ -91,15 +98,18 @@ inline double plan_makespan(const Tb2Plan& P, uint32_t nz, const std::vector<dou
 }
 
 // The plan for a lattice shape: tiles cut into `groups` ranges of equal total
-// cost, and of the chunk lengths tried (every length from 16 planes up to nz
-// that changes the chunk count or the last chunk's length by a step) the one
+// cost, and of the chunk lengths tried (every length from 2 planes up to nz
+// that changes the chunk count or the last chunk's length by a step: below 256^3 the
+// tiles alone are too few for the CUs, and chunks of 16 planes at least had left 100^3
+// at 112 workgroups and 80 us per launch where 240 take 49) the one
 // with the smallest estimated finishing time.
 inline Tb2Plan make_plan(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t tiles_x,
-                         uint32_t tiles_y, uint32_t groups, uint32_t cus) {
+                         uint32_t tiles_y, uint32_t groups, uint32_t cus,
+                         uint32_t tw = TB_TX, uint32_t th = kTbTY) {
     const uint32_t tiles = tiles_x * tiles_y;
     std::vector<double> cost(tiles), cum(tiles + 1, 0.0);
     for (uint32_t t = 0; t < tiles; ++t) {
-        cost[t] = tile_cost(t, tiles_x, nx, ny);
+        cost[t] = tile_cost(t, tiles_x, nx, ny, tw, th);
         cum[t + 1] = cum[t] + cost[t];
     }
     Tb2Plan best;
@@ -128,7 +138,7 @@ inline Tb2Plan make_plan(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t tiles_x
     };
     consider(nz);                          // one chunk: always possible
     const uint32_t step = std::max<uint32_t>(1, nz / 256);
-    for (uint32_t zlen = 16; zlen < nz; zlen += step) consider(zlen);
+    for (uint32_t zlen = 2; zlen < nz; zlen += step) consider(zlen);
     for (uint32_t g = 0; g < groups; ++g) {
         const uint32_t items = (best.w.cut[g + 1] - best.w.cut[g]) * best.w.nchunk;
         best.per_group = std::max(best.per_group, items);
