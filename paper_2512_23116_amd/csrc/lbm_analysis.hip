@@ -165,52 +165,193 @@ __global__ __launch_bounds__(256) void k_sum_rows(const double* partials, int ro
     }
 }
 
-__device__ __forceinline__ double block_sum(double v, double* red) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) red[wv] = v;
-    __syncthreads();
-    return red[0] + red[1] + red[2] + red[3];
+// ------------------------------------------------ structure functions ---
+// The velocity component along an axis is cut into tiles of `w` whole lines of that
+// axis, held as tile[j][line], j along the axis: the separation r is then a shift by
+// r * w elements, periodic over the tile.  A block loads a tile into LDS once and
+// takes every separation from it; its 8 waves share out the separations, two to a
+// wave, and what is left of the waves splits the elements.
+constexpr int kStructRs = 16;          // separations of one launch
+constexpr int kStructThreads = 512;
+constexpr uint32_t kStructLine = 2048;
+
+// One axis: lines of n elements, w of them to a tile.  Lines along y and z are grouped
+// with their neighbours in x, `groups` tiles to a row of nx.
+struct StructAxis {
+    uint32_t n, w, groups;
+};
+
+struct StructArgs {
+    const double* u;
+    uint32_t nx, ny, nz;
+    StructAxis ax[3];
+    uint32_t first[4];           // ax[a]'s tiles are first[a] .. first[a + 1] - 1
+    int32_t nr, pairs, share;    // separations; wave pairs (power of two); waves per pair
+    uint32_t r[kStructRs];
+};
+
+__device__ __forceinline__ void struct_sums(double (&acc)[6], double du) {
+    const double d2 = du * du, ad = fabs(du), d4 = d2 * d2;
+    acc[0] += d2;
+    acc[1] = fma(d2, du, acc[1]);
+    acc[2] = fma(d2, ad, acc[2]);
+    acc[3] += d4;
+    acc[4] = fma(d4, ad, acc[4]);
+    acc[5] = fma(d4, d2, acc[5]);
 }
 
-// Per-block sums of du^2, du^3, |du|^3, du^4, |du|^5, du^6 for the separation
-// rs[blockIdx.y] along each axis, du = u_a(x + r e_a) - u_a(x), periodic.
-__global__ __launch_bounds__(256) void k_structure(const double* u, uint32_t nx, uint32_t ny,
-                                                   uint32_t nz, const int32_t* rs, double* partials) {
-    __shared__ double red[4];
-    const uint32_t r = (uint32_t)rs[blockIdx.y];
-    const uint32_t rx = r % nx, ry = r % ny, rz = r % nz;
-    const uint64_t ncell = (uint64_t)nx * ny * nz;
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (uint64_t c = (uint64_t)blockIdx.x * 256 + threadIdx.x; c < ncell;
-         c += (uint64_t)gridDim.x * 256) {
-        const uint32_t x = (uint32_t)(c % nx);
-        const uint64_t row = c / nx;
-        const uint32_t y = (uint32_t)(row % ny), z = (uint32_t)(row / ny);
-        const uint32_t xs = x + rx >= nx ? x + rx - nx : x + rx;
-        const uint32_t ys = y + ry >= ny ? y + ry - ny : y + ry;
-        const uint32_t zs = z + rz >= nz ? z + rz - nz : z + rz;
-        const uint64_t c_x = (uint64_t)xs + (uint64_t)nx * row;
-        const uint64_t c_y = x + (uint64_t)nx * (ys + (uint64_t)ny * z);
-        const uint64_t c_z = x + (uint64_t)nx * (y + (uint64_t)ny * zs);
-        const double d[3] = {u[c_x] - u[c], u[ncell + c_y] - u[ncell + c],
-                             u[2 * ncell + c_z] - u[2 * ncell + c]};
-        for (int a = 0; a < 3; ++a) {
-            const double du = d[a], d2 = du * du, ad = fabs(du);
-            acc[0] += d2;
-            acc[1] += d2 * du;
-            acc[2] += d2 * ad;
-            acc[3] += d2 * d2;
-            acc[4] += d2 * d2 * ad;
-            acc[5] += d2 * d2 * d2;
+// Sums of du^2, du^3, |du|^3, du^4, |du|^5, du^6 for each separation over the three
+// axes, du = u_a(x + r e_a) - u_a(x), periodic: one row of 6 per wave that shares a
+// separation, partials[r][block][share].  Bound by the FP64 unit (9 instructions per
+// axis, cell and separation) and, next, by LDS (1.5 reads).  256^3 with 14
+// separations: 0.45 ms, of which 0.12 load the tiles; a thread per cell that read
+// u[x + r] from memory for every separation took 1.27.
+__global__ __launch_bounds__(kStructThreads)
+__attribute__((amdgpu_waves_per_eu(8, 8))) void k_structure(StructArgs A, double* partials) {
+    extern __shared__ double tile[];
+    const uint32_t lane = threadIdx.x & 63u;
+    const int wave = (int)(threadIdx.x >> 6);
+    const int pair = wave & (A.pairs - 1), sub = wave / A.pairs;
+    const int j0 = 2 * pair, j1 = j0 + 1;
+    const bool live = j0 < A.nr;
+    const uint32_t r0 = A.r[live ? j0 : 0], r1 = A.r[j1 < A.nr ? j1 : 0];
+    double a0[6] = {0, 0, 0, 0, 0, 0}, a1[6] = {0, 0, 0, 0, 0, 0};
+    const uint64_t nxy = (uint64_t)A.nx * A.ny, ncell = nxy * A.nz;
+    for (uint32_t t = blockIdx.x; t < A.first[3]; t += gridDim.x) {
+        const int a = t >= A.first[2] ? 2 : (t >= A.first[1] ? 1 : 0);
+        const StructAxis& X = A.ax[a];
+        const uint32_t i = t - A.first[a], n = X.n, w = X.w, total = n * w;
+        const double* u = A.u + a * ncell;
+        // element (j, line) of the tile at u[base + j * sj + line], along x at
+        // u[base + line * n + j], line < lines
+        uint64_t base, sj;
+        uint32_t lines;
+        if (a == 0) {
+            base = (uint64_t)i * w * A.nx;
+            sj = 1;
+            const uint64_t left = (uint64_t)A.ny * A.nz - (uint64_t)i * w;
+            lines = left < w ? (uint32_t)left : w;
+        } else {
+            const uint32_t row = i / X.groups, x0 = (i - row * X.groups) * w;
+            base = x0 + (uint64_t)row * (a == 1 ? nxy : A.nx);
+            sj = a == 1 ? A.nx : nxy;
+            lines = A.nx - x0 < w ? A.nx - x0 : w;
+        }
+        __syncthreads();   // the last tile has been read
+        if (a == 0) {
+            for (uint32_t l = (uint32_t)wave; l < w; l += kStructThreads / 64)
+                for (uint32_t j = lane; j < n; j += 64)
+                    tile[j * w + l] = l < lines ? u[base + (uint64_t)l * n + j] : 0.0;
+        } else {
+            const uint32_t jn = kStructThreads / w, jt = threadIdx.x / w;
+            const uint32_t l = threadIdx.x - jt * w;
+            for (uint32_t j = jt < jn ? jt : n; j < n; j += jn)
+                tile[j * w + l] = l < lines ? u[base + j * sj + l] : 0.0;
+        }
+        __syncthreads();
+        if (!live) continue;
+        const uint32_t s0 = r0 % n * w, s1 = r1 % n * w;
+        // 4 x 64 elements at a time: a run that does not straddle the wrap is four
+        // reads off one address
+        for (uint32_t c = (uint32_t)sub * 256u; c < total; c += (uint32_t)A.share * 256u) {
+            const uint32_t b0 = c + s0 >= total ? c + s0 - total : c + s0;
+            const uint32_t b1 = c + s1 >= total ? c + s1 - total : c + s1;
+            if (c + 256 <= total && b0 + 256 <= total && b1 + 256 <= total) {
+#pragma unroll 2
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const double v = tile[c + lane + 64 * k];
+                    struct_sums(a0, tile[b0 + lane + 64 * k] - v);
+                    struct_sums(a1, tile[b1 + lane + 64 * k] - v);
+                }
+            } else {
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const uint32_t o = lane + 64 * k;
+                    if (c + o >= total) break;
+                    const double v = tile[c + o];
+                    struct_sums(a0, tile[b0 + o >= total ? b0 + o - total : b0 + o] - v);
+                    struct_sums(a1, tile[b1 + o >= total ? b1 + o - total : b1 + o] - v);
+                }
+            }
         }
     }
+    if (!live) return;
     for (int m = 0; m < 6; ++m) {
-        const double s = block_sum(acc[m], red);
-        if (threadIdx.x == 0)
-            partials[((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * 6 + m] = s;
+        for (int o = 32; o > 0; o >>= 1) {
+            a0[m] += __shfl_xor(a0[m], o, 64);
+            a1[m] += __shfl_xor(a1[m], o, 64);
+        }
     }
+    if (lane == 0) {
+        const uint64_t rows = (uint64_t)gridDim.x * A.share;
+        const uint64_t row = (uint64_t)blockIdx.x * A.share + sub;
+        for (int m = 0; m < 6; ++m) partials[((uint64_t)j0 * rows + row) * 6 + m] = a0[m];
+        if (j1 < A.nr)
+            for (int m = 0; m < 6; ++m) partials[((uint64_t)j1 * rows + row) * 6 + m] = a1[m];
+    }
+}
+
+// The same sums for the separation r[blockIdx.y], each block a row of
+// partials[r][block]: a thread per cell reads its neighbours along the axes from memory.
+// For one separation, where reading the velocity once more than the tiles do costs less
+// than going through LDS (256^3: 0.12 ms against 0.17), and for lines too long for LDS.
+__global__ __launch_bounds__(256) void k_structure_direct(StructArgs A, DivMagic mx, DivMagic my,
+                                                          double* partials) {
+    __shared__ double red[4][6];
+    const uint32_t r = A.r[blockIdx.y], rx = r % A.nx, ry = r % A.ny, rz = r % A.nz;
+    const uint32_t nxy = A.nx * A.ny, ncell = nxy * A.nz;
+    const double *ux = A.u, *uy = ux + ncell, *uz = uy + ncell;
+    double acc[6] = {0, 0, 0, 0, 0, 0};
+    for (uint32_t c = blockIdx.x * 256u + threadIdx.x; c < ncell; c += gridDim.x * 256u) {
+        const uint32_t row = fast_div(c, mx), z = fast_div(row, my);
+        const uint32_t x = c - row * A.nx, y = row - z * A.ny;
+        const uint32_t cx = x + rx >= A.nx ? c + rx - A.nx : c + rx;
+        const uint32_t cy = y + ry >= A.ny ? c + ry * A.nx - nxy : c + ry * A.nx;
+        const uint32_t cz = z + rz >= A.nz ? c + rz * nxy - ncell : c + rz * nxy;
+        struct_sums(acc, ux[cx] - ux[c]);
+        struct_sums(acc, uy[cy] - uy[c]);
+        struct_sums(acc, uz[cz] - uz[c]);
+    }
+    for (int m = 0; m < 6; ++m) {
+        for (int o = 32; o > 0; o >>= 1) acc[m] += __shfl_xor(acc[m], o, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][m] = acc[m];
+    }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        const int m = (int)threadIdx.x;
+        partials[((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * 6 + m] =
+            red[0][m] + red[1][m] + red[2][m] + red[3][m];
+    }
+}
+
+// The tiles of a lattice's three axes; returns the bytes of LDS they take.  A tile is 32
+// KB (4 blocks to a CU) where that holds 128 bytes of every row (n <= 256), then up to
+// 64 KB, in fewer lines from n = 512.  Lines of more than kStructLine elements take
+// k_structure_direct: four of them would not fit.  Tiles along x hold an odd number of lines, so that the
+// store that transposes them spreads over the LDS banks; along y and z a row is cut
+// into equal tiles.
+static size_t struct_plan(StructArgs& A) {
+    const uint32_t len[3] = {A.nx, A.ny, A.nz};
+    uint32_t most = 0;
+    A.first[0] = 0;
+    for (int a = 0; a < 3; ++a) {
+        StructAxis& X = A.ax[a];
+        X.n = len[a];
+        uint32_t w = X.n <= 256 ? 4096 / X.n : (X.n <= 512 ? 16 : (X.n <= 1024 ? 8 : 4));
+        w = std::min<uint32_t>(w, kStructThreads);
+        // two blocks per CU at least, while a row of the tile keeps 64 bytes
+        while (w > 8 && 3ull * A.nx * A.ny * A.nz < 512ull * X.n * w) w /= 2;
+        if (a == 0) {
+            X.w = w - (w % 2 == 0);
+            X.groups = 1;
+            A.first[1] = (uint32_t)(((uint64_t)A.ny * A.nz + X.w - 1) / X.w);
+        } else {
+            X.groups = (A.nx + w - 1) / w;
+            X.w = (A.nx + X.groups - 1) / X.groups;
+            A.first[a + 1] = A.first[a] + X.groups * (a == 1 ? A.nz : A.ny);
+        }
+        most = std::max(most, X.n * X.w);
+    }
+    return most * sizeof(double);
 }
 
 }  // namespace lbm
@@ -228,13 +369,6 @@ const char* fft_error(hipfftResult r) {
         default: return "hipFFT error";
     }
 }
-
-struct DevBuf {
-    void* p = nullptr;
-    ~DevBuf() {
-        if (p) (void)hipFree(p);
-    }
-};
 
 lbm_status set_err(lbm_handle* h, lbm_status st, const std::string& m) {
     h->err = m;
@@ -606,26 +740,45 @@ lbm_status lbm_structure_functions(lbm_handle* h, const int32_t* rs, int32_t nr,
     for (int j = 0; j < nr; ++j)
         if (rs[j] < 1) return set_err(h, LBM_ERR_INVALID_ARG, "separations must be >= 1");
     if (!h->initialized) return set_err(h, LBM_ERR_STATE, "state not initialised");
-    const uint32_t nx = h->args.nx, ny = h->args.ny, nz = h->args.nz;
-    const size_t nc = h->args.ncell;
-    DevBuf drs, part, res;
     const double* u = nullptr;
     lbm_status st = velocity(h, &u);
     if (st != LBM_OK) return st;
-    const int nb = (int)std::min<size_t>(kAnaBlocks, (nc + 255) / 256);
-    hipError_t e = hipMalloc(&drs.p, nr * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&part.p, (size_t)nr * nb * 6 * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&res.p, (size_t)nr * 6 * sizeof(double));
+    StructArgs A{};
+    A.u = u;
+    A.nx = h->args.nx;
+    A.ny = h->args.ny;
+    A.nz = h->args.nz;
+    const bool tiled = std::max(A.nx, std::max(A.ny, A.nz)) <= kStructLine;
+    const size_t shm = tiled ? struct_plan(A) : 0;
+    constexpr int kWaves = kStructThreads / 64;
+    AnalysisCache& a = cache(h);
+    hipError_t e = ensure(a.part, a.part_elems, (size_t)kAnaBlocks * kWaves * 2 * 6);
+    if (e == hipSuccess) e = ensure(a.out, a.out_elems, (size_t)nr * 6);
     if (e != hipSuccess) return hip_err(h, e, "hipMalloc(structure functions)");
-    e = hipMemcpyAsync(drs.p, rs, nr * sizeof(int32_t), hipMemcpyHostToDevice, h->stream);
-    if (e != hipSuccess) return hip_err(h, e, "copy separations");
-    hipLaunchKernelGGL(k_structure, dim3(nb, nr), dim3(256), 0, h->stream, u, nx,
-                       ny, nz, (const int32_t*)drs.p, (double*)part.p);
-    // rows of 6 sums per (r, block): reduce the blocks of each r in a fixed order
-    hipLaunchKernelGGL(k_sum_rows, dim3(6, nr), dim3(256), 0, h->stream, (const double*)part.p,
-                       nb, 6, 1.0 / (3.0 * nc), 0, (double*)res.p);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(out, res.p, (size_t)nr * 6 * sizeof(double),
+    for (int j = 0; j < nr && e == hipSuccess; j += kStructRs) {
+        A.nr = std::min(nr - j, kStructRs);
+        A.pairs = 1;
+        while (2 * A.pairs < A.nr) A.pairs *= 2;
+        A.share = kWaves / A.pairs;
+        for (int k = 0; k < A.nr; ++k) A.r[k] = (uint32_t)rs[j + k];
+        int rows;
+        if (tiled && A.nr > 1) {
+            const int nb = (int)std::min<uint32_t>(kAnaBlocks, A.first[3]);
+            rows = nb * A.share;
+            hipLaunchKernelGGL(k_structure, dim3(nb), dim3(kStructThreads), shm, h->stream, A,
+                               a.part);
+        } else {
+            rows = (int)std::min<uint32_t>(kAnaBlocks, (h->args.ncell + 255) / 256);
+            hipLaunchKernelGGL(k_structure_direct, dim3(rows, A.nr), dim3(256), 0, h->stream, A,
+                               h->args.mx, h->args.my, a.part);
+        }
+        // rows of 6 sums per (r, row): reduce the rows of each r in a fixed order
+        hipLaunchKernelGGL(k_sum_rows, dim3(6, A.nr), dim3(256), 0, h->stream,
+                           (const double*)a.part, rows, 6, 1.0 / (3.0 * h->args.ncell), 0,
+                           a.out + (size_t)j * 6);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(out, a.out, (size_t)nr * 6 * sizeof(double),
                                             hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_err(h, e, "structure functions");
