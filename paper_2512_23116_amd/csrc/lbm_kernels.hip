@@ -215,15 +215,21 @@ __global__ __launch_bounds__(256) void k_ktslice(LatticeArgs L, uint32_t z, floa
 // Fixed-bin histogram of theta: counts[0] below lo, counts[1 + b] for
 // b = floor((theta - lo) * inv_w) in 0..nbins-1, counts[nbins + 1] at or above
 // the top edge, counts[nbins + 2] non-finite.  Per-block LDS counts, then one
-// 64-bit integer atomic per non-empty bin: the totals are exact.
+// 64-bit integer atomic per non-empty bin: the totals are exact.  The reads bound it
+// once those atomics, all of them on the same few hundred words, are few: a block per CU
+// takes its share of the cells (256^3 FP32: 254 us a call, 100^3: 45; a block
+// per 256 cells took 1430 and 116).
+constexpr int kHistThreads = 1024, kHistBlocks = 256;
+
 template <class Cd, int PAT>
-__global__ __launch_bounds__(256) void k_theta_hist(LatticeArgs L, double lo, double inv_w,
-                                                    int nbins, unsigned long long* counts) {
-    extern __shared__ unsigned int hist[];
-    for (int k = threadIdx.x; k < nbins + 3; k += 256) hist[k] = 0u;
+__global__ __launch_bounds__(kHistThreads) void k_theta_hist(LatticeArgs L, double lo,
+                                                             double inv_w, int nbins,
+                                                             unsigned long long* counts) {
+    extern __shared__ unsigned int hist[];   // a block has fewer than 2^32 cells
+    for (int k = threadIdx.x; k < nbins + 3; k += kHistThreads) hist[k] = 0u;
     __syncthreads();
-    const uint32_t cell = blockIdx.x * 256u + threadIdx.x;
-    if (cell < L.ncell) {
+    for (uint32_t cell = blockIdx.x * kHistThreads + threadIdx.x; cell < L.ncell;
+         cell += gridDim.x * kHistThreads) {
         const double theta = cell_theta<Cd, PAT>(L, cell);
         int b;
         if (!isfinite(theta)) {
@@ -237,7 +243,7 @@ __global__ __launch_bounds__(256) void k_theta_hist(LatticeArgs L, double lo, do
         atomicAdd(&hist[b], 1u);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < nbins + 3; k += 256)
+    for (int k = threadIdx.x; k < nbins + 3; k += kHistThreads)
         if (hist[k]) atomicAdd(&counts[k], (unsigned long long)hist[k]);
 }
 
@@ -493,7 +499,8 @@ hipError_t launch_theta_hist(int precision, int pat, const LatticeArgs& L, doubl
     return dispatch(precision, pat, [&](auto cd, auto pt) {
         using Cd = decltype(cd);
         constexpr int P = decltype(pt)::value;
-        hipLaunchKernelGGL((k_theta_hist<Cd, P>), grid_for(L.ncell), dim3(256),
+        const uint32_t nb = std::min<uint32_t>(kHistBlocks, (L.ncell + kHistThreads - 1) / kHistThreads);
+        hipLaunchKernelGGL((k_theta_hist<Cd, P>), dim3(nb), dim3(kHistThreads),
                            (size_t)(nbins + 3) * sizeof(unsigned int), s, L, lo, inv_w, nbins,
                            counts);
         return hipGetLastError();
