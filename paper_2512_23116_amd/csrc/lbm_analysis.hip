@@ -93,10 +93,12 @@ __global__ __launch_bounds__(256) void k_shell_bin(const hipfftDoubleComplex* c,
 // w = 2 for the kx > 0 modes that stand for a conjugate pair (both members
 // have the same |k_a|).  In a row every lane has its own |k_x| bin, and the
 // whole row shares one |k_y| and one |k_z| bin: lane 0 adds the row's total,
-// folded chunk by chunk over a fixed butterfly.
-__global__ __launch_bounds__(256) void k_axis_bin(const hipfftDoubleComplex* c, uint32_t nx,
-                                                  uint32_t ny, uint32_t nz, int kmax,
+// folded chunk by chunk over a fixed butterfly.  blockIdx.y takes the transform
+// blockIdx.y * cstride on, into partials[blockIdx.y] of gridDim.x blocks each.
+__global__ __launch_bounds__(256) void k_axis_bin(const hipfftDoubleComplex* c, uint64_t cstride,
+                                                  uint32_t nx, uint32_t ny, uint32_t nz, int kmax,
                                                   double inv_n2, double* partials) {
+    c += blockIdx.y * cstride;
     extern __shared__ double hist[];   // [waves][3][kmax + 1]
     const int nb = 3 * (kmax + 1), waves = (int)(blockDim.x >> 6);
     for (int k = threadIdx.x; k < waves * nb; k += blockDim.x) hist[k] = 0.0;
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(256) void k_axis_bin(const hipfftDoubleComplex* c, 
     for (int k = threadIdx.x; k < nb; k += blockDim.x) {
         double s = hist[k];
         for (int w = 1; w < waves; ++w) s += hist[w * nb + k];
-        partials[(uint64_t)blockIdx.x * nb + k] = s;
+        partials[((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * nb + k] = s;
     }
 }
 
@@ -682,24 +684,30 @@ lbm_status lbm_spectra_1d(lbm_handle* h, int32_t kmax, double* E, double* ic) {
     lbm_status st = velocity(h, &u);
     if (st != LBM_OK) return st;
     AnalysisCache& a = cache(h);
-    hipError_t e = ensure(a.c, a.c_elems, nmodes);
-    if (e == hipSuccess) e = ensure(a.part, a.part_elems, (size_t)kAnaBlocks * cols);
+    // one call for the three transforms and one for each sum over them (32^3 111 ->
+    // 45 us, 128^3 222 -> 153, 240^3 885 -> 857); from 2^24 cells a component at a time,
+    // whose sums fold what is still in the cache (256^3 1110 us, batched 1130)
+    const bool batched = h->args.ncell < (size_t(1) << 24);
+    const int passes = batched ? 1 : 3, ncomp = batched ? 3 : 1;
+    hipError_t e = ensure(a.c, a.c_elems, ncomp * nmodes);
+    if (e == hipSuccess) e = ensure(a.part, a.part_elems, (size_t)ncomp * kAnaBlocks * cols);
     if (e == hipSuccess) e = ensure(a.out, a.out_elems, (size_t)3 * cols);
     if (e != hipSuccess) return hip_err(h, e, "hipMalloc(one-dimensional spectra)");
-    st = fft_plan(h, a, h->stream);
+    st = batched ? fft_plan3(h, a, h->stream) : fft_plan(h, a, h->stream);
     if (st != LBM_OK) return st;
     const double inv_n2 = 1.0 / ((double)nc * (double)nc);
+    const size_t hb = (size_t)cols * sizeof(double);
+    const int bt = bin_threads(hb);
     hipfftResult fr = HIPFFT_SUCCESS;
-    for (int c = 0; c < 3 && fr == HIPFFT_SUCCESS; ++c) {
-        fr = hipfftExecD2Z(a.plan, (hipfftDoubleReal*)(u + (size_t)c * nc), a.c);
+    for (int c = 0; c < passes && fr == HIPFFT_SUCCESS; ++c) {
+        fr = hipfftExecD2Z(batched ? a.plan3 : a.plan, (hipfftDoubleReal*)(u + (size_t)c * nc), a.c);
         if (fr != HIPFFT_SUCCESS) break;
-        const size_t hb = (size_t)cols * sizeof(double);
-        const int bt = bin_threads(hb);
-        hipLaunchKernelGGL(k_axis_bin, dim3(kAnaBlocks), dim3(bt), hb * (bt / 64), h->stream,
-                           (const hipfftDoubleComplex*)a.c, nx, ny, nz, (int)kmax, inv_n2,
-                           a.part);
-        hipLaunchKernelGGL(k_sum_rows, dim3(cols), dim3(256), 0, h->stream, (const double*)a.part,
-                           kAnaBlocks, cols, 1.0, 0, a.out + (size_t)c * cols);
+        hipLaunchKernelGGL(k_axis_bin, dim3(kAnaBlocks, ncomp), dim3(bt), hb * (bt / 64), h->stream,
+                           (const hipfftDoubleComplex*)a.c, (uint64_t)nmodes, nx, ny, nz,
+                           (int)kmax, inv_n2, a.part);
+        hipLaunchKernelGGL(k_sum_rows, dim3(cols, ncomp), dim3(256), 0, h->stream,
+                           (const double*)a.part, kAnaBlocks, cols, 1.0, 0,
+                           a.out + (size_t)c * cols);
     }
     if (fr != HIPFFT_SUCCESS) return set_err(h, LBM_ERR_DEVICE, std::string("hipFFT: ") + fft_error(fr));
     e = hipGetLastError();
