@@ -110,9 +110,8 @@ typedef struct {
                                 FP32/FP16/BF16; steps_per_graph a multiple of
                                 4 or 0): the intermediate level stays in LDS,
                                 halving HBM traffic per step at ~19% more
-                                arithmetic.  Results equal single steps up to
-                                the rounding of the FP32 collision, and do not
-                                depend on how a launch splits the work.        */
+                                arithmetic.  Results have the bits of single
+                                steps, however a launch splits the work.       */
     int32_t tau_mode;        /* which relaxation rate enters the strain
                                 estimate of App. B.1 eq. yu_strain:
                                 0: s_1 = s_e and s_9 = 1/tau0 (explicit,
@@ -211,8 +210,9 @@ lbm_status lbm_stream_only(lbm_handle* h, int64_t n);
 lbm_status lbm_moments(lbm_handle* h, double* rho, double* u);
 
 /* Domain statistics of theta and K_t plus mass, momentum and energy, reduced
- * on the device in FP64 in a fixed order (bitwise reproducible).  tau_e is
- * computed by the same device code as the step.  Returns LBM_ERR_UNSTABLE
+ * on the device in FP64 in a fixed order (bitwise reproducible).  tau_e
+ * comes from the step's equations; it may differ from the value a step uses in
+ * the last bits.  Returns LBM_ERR_UNSTABLE
  * (with *out filled) when any cell is non-finite.  Synchronises. */
 lbm_status lbm_kt_stats(lbm_handle* h, lbm_stats* out);
 
