@@ -325,7 +325,8 @@ lbm_status lbm_spectra_1d(lbm_handle* h, int32_t kmax, double* E, double* ic);
  *   du = u_a(x + r e_a) - u_a(x) (periodic),  p = (du^2, du^3, |du|^3, du^4, |du|^5, du^6).
  * F4(r) = out[6j+3] / out[6j]^2.  FP64, reduced in a fixed order (bitwise
  * reproducible).  nr in 1..65535.  Uses the handle's analysis velocity buffer
- * (created on first use, 24 bytes per cell) and temporaries.  Synchronises. */
+ * (created on first use, 24 bytes per cell) and under 1 MB of partial sums that
+ * the handle keeps.  Synchronises. */
 lbm_status lbm_structure_functions(lbm_handle* h, const int32_t* rs, int32_t nr, double* out);
 
 /* Turbulence scales of the current state (Sec. 2.2, eq. integral_length_scale,
