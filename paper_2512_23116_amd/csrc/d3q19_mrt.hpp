@@ -12,7 +12,9 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
+#include <stdlib.h>
 
 namespace lbm {
 
@@ -42,7 +44,7 @@ __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sq
 __device__ __forceinline__ double fast_sqrt(double x) { return sqrt(x); }
 
 // Constants of one lattice's collision, in the arithmetic type R.  Those that collide
-// reads come first, 96 bytes in FP32 (see LatticeArgs); cell_macro and the derivation
+// reads come first, 92 bytes in FP32 (see LatticeArgs); cell_macro and the derivation
 // read the rest.
 template <typename R>
 struct CollideConst {
@@ -55,7 +57,7 @@ struct CollideConst {
     R ed_sa, ed_sd, ed_r, ed_u2, ed_uF;   // even part of the diagonal pairs
     R pi_m, pi_F;                         // rows 10 and 12: moment and force
     R o_s, o_F;                           // odd part of the axis pairs
-    R a_j, a_s, a_F, a_m;                 // odd part of the diagonal pairs
+    R a_s, a_F, a_m;                      // odd part of the diagonal pairs
     R w_tr, c_tau;                        // tau_e - tau0 = c_tau sqrt(w), see collide
     R c3;        // 3 C (linear form) or 3 C^2; tau_e = tau0 + c3 |S|
     R a_e;       // s_e / (38 rho0): coefficient of m1_neq in S_aa (eq. yu_strain);
@@ -98,41 +100,58 @@ inline void fill_collide_coefficients(CollideConst<double>& k) {
     }
     k.pi_m = 1.0 - k.s_pi;
     k.pi_F = -(1.0 - 0.5 * k.s_pi);
-    // odd rows: j* = rho u + F/2, q* of rows 4, 6, 8, and rows 16..18 through
-    // m16 - m17 = 4 d3 + d0 + d1 - jx - jy and its five counterparts, in terms of
-    // rho u_x, s0 = rho u_x - 3 d0 and F_x per axis
-    const double q = k.s_q, sm = (1.0 - k.s_m) / 8.0;
+    // odd rows: j* = rho u + F/2 and q* of rows 4, 6, 8 in terms of d0,
+    // s0 = rho u_x - 3 d0 and F_x per axis; rows 16..18 as they are
+    const double q = k.s_q;
     k.o_s = q / 6.0;
     k.o_F = (2.0 - q) / 12.0;
-    k.a_j = k.s_m / 12.0;
-    k.a_s = ((1.0 - q) / 8.0 - sm) / 3.0;
-    k.a_F = ((1.0 + q) / 24.0 + sm) / 2.0;
-    k.a_m = 0.5 - 6.0 * k.a_j;
+    k.a_s = (3.0 - q) / 24.0;
+    k.a_F = (1.0 + q) / 48.0;
+    k.a_m = (1.0 - k.s_m) / 8.0;
     // |S|^2 = 6 (a_e n1)^2 + b9^2 (3 n9^2 + 9 n11^2 + 36 (n13^2 + n14^2 + n15^2)),
     // n1 = 19 (sd - r - rho u^2)
     k.w_tr = 2.0 * (19.0 * k.a_e / k.b9) * (19.0 * k.a_e / k.b9);
     k.c_tau = k.c3 * k.b9 * 1.7320508075688772;
 }
 
-// The same constants in FP32 arithmetic: each rounded once from its FP64 value, but
-// for a_m.
+// One input's coefficients of the axis pairs (a) and the diagonal pairs (d) in FP32:
+// of the values within 2 ulp of each, the two that also leave 6 a + 12 d nearest to
+// its own value.  The rest population is what mass leaves after those 18, so that is
+// its coefficient; rounded on their own, a and d left it up to 4e-8 off and its error
+// after one step 1.3 times what rounding alone gives.
+inline void round_even(double a, double d, float* fa, float* fd) {
+    double best = INFINITY;
+    for (int i = -2; i <= 2; ++i)
+        for (int j = -2; j <= 2; ++j) {
+            float x = (float)a, y = (float)d;
+            for (int n = 0; n < abs(i); ++n) x = nextafterf(x, i < 0 ? -INFINITY : INFINITY);
+            for (int n = 0; n < abs(j); ++n) y = nextafterf(y, j < 0 ? -INFINITY : INFINITY);
+            const double ea = 6.0 * (x - a), ed = 12.0 * (y - d);
+            const double cost = fabs(ea + ed) + 0.02 * (fabs(ea) + fabs(ed));
+            if (cost < best) {
+                best = cost;
+                *fa = x;
+                *fd = y;
+            }
+        }
+}
+
+// The same constants in FP32 arithmetic: each rounded once from its FP64 value, the
+// even parts' coefficients in pairs.
 inline CollideConst<float> round_constants(const CollideConst<double>& k) {
     CollideConst<float> f{};
     f.tau0 = (float)k.tau0; f.c3 = (float)k.c3; f.a_e = (float)k.a_e; f.b9 = (float)k.b9;
     f.s_e = (float)k.s_e; f.s_eps = (float)k.s_eps; f.s_q = (float)k.s_q;
     f.s_pi = (float)k.s_pi; f.s_m = (float)k.s_m; f.rho0 = (float)k.rho0;
     f.tau0_sq = (float)k.tau0_sq; f.self_consistent = k.self_consistent;
-    f.ea_sa = (float)k.ea_sa; f.ea_sd = (float)k.ea_sd; f.ea_r = (float)k.ea_r;
-    f.ea_u2 = (float)k.ea_u2; f.ea_uF = (float)k.ea_uF;
-    f.ed_sa = (float)k.ed_sa; f.ed_sd = (float)k.ed_sd; f.ed_r = (float)k.ed_r;
-    f.ed_u2 = (float)k.ed_u2; f.ed_uF = (float)k.ed_uF;
+    round_even(k.ea_sa, k.ed_sa, &f.ea_sa, &f.ed_sa);
+    round_even(k.ea_sd, k.ed_sd, &f.ea_sd, &f.ed_sd);
+    round_even(k.ea_r, k.ed_r, &f.ea_r, &f.ed_r);
+    round_even(k.ea_u2, k.ed_u2, &f.ea_u2, &f.ed_u2);
+    round_even(k.ea_uF, k.ed_uF, &f.ea_uF, &f.ed_uF);
     f.pi_m = (float)k.pi_m; f.pi_F = (float)k.pi_F;
     f.o_s = (float)k.o_s; f.o_F = (float)k.o_F;
-    f.a_j = (float)k.a_j; f.a_s = (float)k.a_s; f.a_F = (float)k.a_F;
-    // exact in FP32 (a multiple of 2^-25 below 1/2), so that the momentum
-    // 2 o0 + 8 ax + 2 a_m (rho u_x - d0) keeps its rho u_x: a_m rounded on its own
-    // let it drift by up to 6e-8 a step
-    f.a_m = (float)(0.5 - 6.0 * (double)f.a_j);
+    f.a_s = (float)k.a_s; f.a_F = (float)k.a_F; f.a_m = (float)k.a_m;
     f.w_tr = (float)k.w_tr; f.c_tau = (float)k.c_tau;
     return f;
 }
@@ -230,12 +249,18 @@ __device__ __forceinline__ double mad(double a, double b, double c) { return __b
 //   diagonal pairs, even: ed +- ...
 //   rows 9 / 10:  m9 = a + b, m10 = b - 2 a,  a = 3 p0 - sa, b = sd - 3 B
 //   rows 11 / 12: m11 = c + d, m12 = d - 2 c, c = p1 - p2,   d = A - C
-//   odd parts:    o0 and ax, forms of rho u_x, s = rho u_x - 3 d0 and F_x per axis;
-//                 a_m d_k plus the sum or difference of two axes' ax per diagonal pair
-// and |S|^2 needs n1 = 19 (sd - r - rho u^2), n9, n11, n13..15 squared only.  That is
-// 208 floating-point instructions per cell where the row-by-row form took 288.  The
-// rest population is what mass leaves after the others, so that the rounding of the
-// coefficients cannot drift it (for momentum see round_constants).
+//   odd parts:    o0 and ax, forms of d0, s = rho u_x - 3 d0 and F_x per axis;
+//                 sums and differences of ax +- a_m m16, ay +- a_m m17, az +- a_m m18
+// and |S|^2 needs n1 = 19 (sd - r - rho u^2), n9, n11, n13..15 squared only.  205
+// floating-point instructions as compiled, where the row-by-row form took 268.
+// Rounding: the populations are of order u, what changes in a step is much less, so
+// the odd parts start from the old ones (d0/2 and d0/4, exact) and add terms that are
+// zero in equilibrium: s, m16..18.  Momentum, 2 o0 + 8 ax = rho u_x + (2 o_s + 8 a_s - 1) s
+// + ..., then keeps its rho u_x whatever the rates round to, and mass is kept by the rest
+// population, which is what it leaves after the others.  Against 64 bits, 16 steps at
+// 48^3: axis, diagonal and rest populations 1.2e-7, 1.6e-7, 4.5e-7 off in FP32 (the
+// row-by-row form 2.9e-7, 3.1e-7, 7.1e-7), 2.2e-16, 3.0e-16, 8.3e-16 in FP64 (8.0e-16,
+// 8.5e-16, 1.7e-15).
 // Every product-sum is an explicit fused multiply-add and contraction is off, so
 // all kernels that inline this give the same bits.
 //
@@ -323,18 +348,23 @@ __device__ __forceinline__ void collide(R (&g)[19], R Fx, R Fy, R Fz, const Coll
     const R e3 = mad(R(0.25), q13, exy), e4 = mad(R(-0.25), q13, exy);
     const R e5 = mad(R(0.25), q14, eyz), e6 = mad(R(-0.25), q14, eyz);
     const R e7 = mad(R(0.25), q15, exz), e8 = mad(R(-0.25), q15, exz);
-    // odd part per pair, as the old one plus what its departure from equilibrium
-    // (s = 0) and the force change: what is rounded is small
+    // odd part per pair
     const R sx = mad(R(-3), d0, rux), sy = mad(R(-3), d1, ruy), sz = mad(R(-3), d2, ruz);
     const R o0 = mad(R(0.5), d0, mad(k.o_F, Fx, k.o_s * sx));
     const R o1 = mad(R(0.5), d1, mad(k.o_F, Fy, k.o_s * sy));
     const R o2 = mad(R(0.5), d2, mad(k.o_F, Fz, k.o_s * sz));
-    const R ax = mad(k.a_j, rux, mad(k.a_F, Fx, k.a_s * sx));
-    const R ay = mad(k.a_j, ruy, mad(k.a_F, Fy, k.a_s * sy));
-    const R az = mad(k.a_j, ruz, mad(k.a_F, Fz, k.a_s * sz));
-    const R o3 = mad(k.a_m, d3, ax + ay), o4 = mad(k.a_m, d4, ax - ay);
-    const R o5 = mad(k.a_m, d5, ay + az), o6 = mad(k.a_m, d6, ay - az);
-    const R o7 = mad(k.a_m, d7, ax + az), o8 = mad(k.a_m, d8, ax - az);
+    const R ax = mad(R(0.25), d0, mad(k.a_F, Fx, k.a_s * sx));
+    const R ay = mad(R(0.25), d1, mad(k.a_F, Fy, k.a_s * sy));
+    const R az = mad(R(0.25), d2, mad(k.a_F, Fz, k.a_s * sz));
+    const R m16 = (d3 + d4) - (d7 + d8);
+    const R m17 = (d5 + d6) - (d3 - d4);
+    const R m18 = (d7 - d8) - (d5 - d6);
+    const R xp = mad(k.a_m, m16, ax), xm = mad(-k.a_m, m16, ax);
+    const R yp = mad(k.a_m, m17, ay), ym = mad(-k.a_m, m17, ay);
+    const R zp = mad(k.a_m, m18, az), zm = mad(-k.a_m, m18, az);
+    const R o3 = xp + ym, o4 = xp - ym;
+    const R o5 = yp + zm, o6 = yp - zm;
+    const R o7 = xm + zp, o8 = xm - zp;
 
     g[0] = e0 + o0;  g[1] = e0 - o0;
     g[2] = e1 + o1;  g[3] = e1 - o1;

@@ -235,7 +235,7 @@ __device__ __forceinline__ CollideConst<float> early(const CollideConst<float>& 
     CollideConst<float> k = c;
     asm volatile("" : "+s"(k.ea_sa), "+s"(k.ea_sd), "+s"(k.ea_r), "+s"(k.ea_u2), "+s"(k.ea_uF),
                       "+s"(k.ed_sa), "+s"(k.ed_sd), "+s"(k.ed_r), "+s"(k.ed_u2), "+s"(k.ed_uF));
-    asm volatile("" : "+s"(k.pi_m), "+s"(k.pi_F), "+s"(k.o_s), "+s"(k.o_F), "+s"(k.a_j),
+    asm volatile("" : "+s"(k.pi_m), "+s"(k.pi_F), "+s"(k.o_s), "+s"(k.o_F),
                       "+s"(k.a_s), "+s"(k.a_F), "+s"(k.a_m), "+s"(k.w_tr), "+s"(k.c_tau),
                       "+s"(k.tau0), "+s"(k.rho0));
     return k;

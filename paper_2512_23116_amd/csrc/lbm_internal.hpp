@@ -47,8 +47,8 @@ struct LatticeArgs {
     int32_t nt_mode;         // step kernel: bit 1 non-temporal stores
     uint32_t elem_bytes;     // bytes per stored population
 };
-static_assert(offsetof(LatticeArgs, kf) == 64 && offsetof(CollideConst<float>, c3) == 96,
-              "step arguments fill their cache lines");
+static_assert(offsetof(LatticeArgs, kf) == 64 && offsetof(CollideConst<float>, c3) <= 96,
+              "step arguments fit their cache lines");
 
 // Kernel launchers (lbm_kernels.hip).  All return the launch status.
 hipError_t launch_tables(int precision, const LatticeArgs& L, const lbm_force_mode* d_modes,
