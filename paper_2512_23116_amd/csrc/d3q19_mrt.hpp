@@ -43,6 +43,11 @@ __device__ __forceinline__ double fast_rcp(double x) { return 1.0 / x; }
 __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double fast_sqrt(double x) { return sqrt(x); }
 
+// Bits of CollideConst::closure, 0 for the usual lattice.
+constexpr int32_t kSelfConsistent = 1;   // s_9 = 1/tau_e in eq. yu_strain, closed form
+constexpr int32_t kRescaled = 2;         // collide divides the moments of the strain norm by
+constexpr int32_t kScaleShift = 8;       // 2^(closure >> kScaleShift)
+
 // Constants of one lattice's collision, in the arithmetic type R.  Those that collide
 // reads come first, 92 bytes in FP32 (see LatticeArgs); cell_macro and the derivation
 // read the rest.
@@ -51,14 +56,15 @@ struct CollideConst {
     R tau0;      // bare relaxation time
     R rho0;
     R tau0_sq;   // tau0^2
-    int32_t self_consistent;   // 1: s_9 = 1/tau_e in eq. yu_strain, closed form
+    int32_t closure;           // kSelfConsistent, kRescaled and its exponent
     // coefficients of collide, formed in FP64 by fill_collide_coefficients
     R ea_sa, ea_sd, ea_r, ea_u2, ea_uF;   // even part of the axis pairs
     R ed_sa, ed_sd, ed_r, ed_u2, ed_uF;   // even part of the diagonal pairs
     R pi_m, pi_F;                         // rows 10 and 12: moment and force
     R o_s, o_F;                           // odd part of the axis pairs
     R a_s, a_F, a_m;                      // odd part of the diagonal pairs
-    R w_tr, c_tau;                        // tau_e - tau0 = c_tau sqrt(w), see collide
+    R w_tr, c_tau;                        // tau_e - tau0 = c_tau sqrt(w), see collide;
+                                          // kRescaled: w_tr is its square root
     R c3;        // 3 C (linear form) or 3 C^2; tau_e = tau0 + c3 |S|
     R a_e;       // s_e / (38 rho0): coefficient of m1_neq in S_aa (eq. yu_strain);
                  // 0 in the self-consistent mode
@@ -80,7 +86,8 @@ struct CellMacro {
 // eq. mrt_les_guo is m* = (1 - s) m + s m_eq + (1 - s/2) F_m, a linear form of the
 // pair sums and differences, the momentum, rho u u and u F; the rows with fixed
 // rates are folded here into one coefficient per input and output.
-inline void fill_collide_coefficients(CollideConst<double>& k) {
+// scale: the storage scale, in whose units collide's kScaled works.
+inline void fill_collide_coefficients(CollideConst<double>& k, double scale = 1.0) {
     const double ge = 1.0 - 0.5 * k.s_e, geps = 1.0 - 0.5 * k.s_eps;
     // t1 = m1*/2394, t2 = m2*/252 as forms of (sa, sd, r, rho u^2, u.F), with
     // m1 = -11 sa + 8 sd - 30 r, m2 = -4 sa + sd + 12 r, t0 = (sa + sd + r)/19
@@ -112,6 +119,18 @@ inline void fill_collide_coefficients(CollideConst<double>& k) {
     // n1 = 19 (sd - r - rho u^2)
     k.w_tr = 2.0 * (19.0 * k.a_e / k.b9) * (19.0 * k.a_e / k.b9);
     k.c_tau = k.c3 * k.b9 * 1.7320508075688772;
+    // w is of the order of (rho0 scale)^2, its trace part of tau0^2 times that: out of
+    // FP32 from rho0 = 2^64 or tau0 = 2^64 up, and at rho0 = 2^-43 a strain of 1e-6 is
+    // lost.  Well before that it is formed of moments divided by a power of two.
+    int e, et;
+    frexp(k.tau0, &et);
+    frexp(k.rho0 * scale, &e);
+    if (e > 32 || e < -16 || et > 20) {
+        e += et > 0 ? et : 0;
+        k.closure |= kRescaled | e * (1 << kScaleShift);
+        k.w_tr = sqrt(k.w_tr);
+        k.c_tau = ldexp(k.c_tau, e) / scale;
+    }
 }
 
 // One input's coefficients of the axis pairs (a) and the diagonal pairs (d) in FP32:
@@ -143,7 +162,7 @@ inline CollideConst<float> round_constants(const CollideConst<double>& k) {
     f.tau0 = (float)k.tau0; f.c3 = (float)k.c3; f.a_e = (float)k.a_e; f.b9 = (float)k.b9;
     f.s_e = (float)k.s_e; f.s_eps = (float)k.s_eps; f.s_q = (float)k.s_q;
     f.s_pi = (float)k.s_pi; f.s_m = (float)k.s_m; f.rho0 = (float)k.rho0;
-    f.tau0_sq = (float)k.tau0_sq; f.self_consistent = k.self_consistent;
+    f.tau0_sq = (float)k.tau0_sq; f.closure = k.closure;
     round_even(k.ea_sa, k.ed_sa, &f.ea_sa, &f.ed_sa);
     round_even(k.ea_sd, k.ed_sd, &f.ea_sd, &f.ed_sd);
     round_even(k.ea_r, k.ed_r, &f.ea_r, &f.ed_r);
@@ -218,7 +237,7 @@ __device__ __forceinline__ CellMacro<R> cell_macro(const R (&g)[19], R Fx, R Fy,
                  R(4) * (Sxy * Sxy + Sxz * Sxz + Syz * Syz);
     // eq. les_viscosity: tau_e = 1/2 + 3 (nu0 + C Delta^2 |S|) = tau0 + 3 C |S|
     R tau_t = k.c3 * fast_sqrt(S2);
-    if (k.self_consistent) {
+    if (k.closure & kSelfConsistent) {
         // (the empty asm keeps this a uniform branch instead of computing it
         // always and selecting, so the default mode pays nothing for it)
         asm volatile("");
@@ -230,12 +249,14 @@ __device__ __forceinline__ CellMacro<R> cell_macro(const R (&g)[19], R Fx, R Fy,
     }
     const R tau_e = k.tau0 + tau_t;
     // |S|^2: S2 itself, or (|S_1| / tau_e)^2 in the self-consistent mode
-    const R snorm2 = k.self_consistent ? S2 * fast_rcp(tau_e * tau_e) : S2;
+    const R snorm2 = (k.closure & kSelfConsistent) ? S2 * fast_rcp(tau_e * tau_e) : S2;
     return CellMacro<R>{m0, rho, ux, uy, uz, tau_t, snorm2};
 }
 
 __device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float scale2(float a, int e) { return __builtin_ldexpf(a, e); }
+__device__ __forceinline__ double scale2(double a, int e) { return __builtin_ldexp(a, e); }
 
 // Collide one cell in place (eq. mrt_les_guo).  g: deviation populations
 // (pre-collision in, post-collision out).  F: body force at the cell.
@@ -314,12 +335,22 @@ __device__ __forceinline__ void collide(R (&g)[19], R Fx, R Fy, R Fz, const Coll
     const R n13 = mad(-rux, uy, m13), n14 = mad(-ruy, uz, m14), n15 = mad(-rux, uz, m15);
 
     // eq. yu_strain, eq. strain_norm, eq. les_viscosity: tau_e = tau0 + c_tau sqrt(w)
-    const R off = mad(n13, n13, mad(n14, n14, n15 * n15));
-    const R w = mad(k.w_tr, n1 * n1, mad(R(12), off, mad(R(3), n11 * n11, n9 * n9)));
-    R tau_t = (kScaled ? k.c_tau * is : k.c_tau) * fast_sqrt(w);
-    if (k.self_consistent) {
-        // (the empty asm keeps this a uniform branch instead of computing it
-        // always and selecting, so the default mode pays nothing for it)
+    // (the empty asm keeps the two branches uniform ones instead of computing both sides
+    // and selecting, so the usual lattice pays nothing for them)
+    R trace = n1 * n1, w_tr = k.w_tr, c_tau = kScaled ? k.c_tau * is : k.c_tau;
+    R shear = mad(R(12), mad(n13, n13, mad(n14, n14, n15 * n15)), mad(R(3), n11 * n11, n9 * n9));
+    if (__builtin_expect((k.closure & kRescaled) != 0, 0)) {
+        asm volatile("");
+        const int e = -(k.closure >> kScaleShift);
+        const R t1 = k.w_tr * scale2(n1, e), t9 = scale2(n9, e), t11 = scale2(n11, e);
+        const R t13 = scale2(n13, e), t14 = scale2(n14, e), t15 = scale2(n15, e);
+        trace = t1 * t1;
+        w_tr = R(1);
+        shear = mad(R(12), mad(t13, t13, mad(t14, t14, t15 * t15)), mad(R(3), t11 * t11, t9 * t9));
+        c_tau = k.c_tau;
+    }
+    R tau_t = c_tau * fast_sqrt(mad(w_tr, trace, shear));
+    if (k.closure & kSelfConsistent) {
         asm volatile("");
         // the positive root of tau_e^2 - tau0 tau_e - c3 |S_1| = 0 as its
         // increment over tau0, as in cell_macro

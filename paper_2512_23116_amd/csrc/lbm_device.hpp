@@ -227,10 +227,13 @@ __device__ __forceinline__ void force_at(const LatticeArgs& L, const CellPos& p,
     Fz = rc[2] + s1 * rc[5] + c1 * rc[8] + s2 * rc[11] + c2 * rc[14];
 }
 
-// The collision's constants, read before the populations are waited for.  Left where
-// they are first used, their scalar loads come after that wait and add to it: the
-// 100^3 FP32 A/B step then takes 24.1 us instead of 23.7, 129x127x130 AA 48.8
-// instead of 48.3.  (FP64 has the registers for neither; see k_step.)
+// The collision's constants, read before the populations are waited for, and the planes
+// an A/B step stores to, read before the collision.  Left where they are first used,
+// their scalar loads come after that wait, or between the collision and the stores, and
+// add to the launch: 100^3 FP32 A/B then takes 23.95 us for either instead of 23.70,
+// 129x127x130 AA 48.24 instead of 48.14 without the constants.  FP64 has no registers for
+// the constants (k_step), and 16-bit storage, which has more conversions to hide behind,
+// gains nothing from the planes (256^3 FP16 A/B 245.2 against 244.6).
 __device__ __forceinline__ CollideConst<float> early(const CollideConst<float>& c) {
     CollideConst<float> k = c;
     asm volatile("" : "+s"(k.ea_sa), "+s"(k.ea_sd), "+s"(k.ea_r), "+s"(k.ea_u2), "+s"(k.ea_uF),
@@ -239,6 +242,16 @@ __device__ __forceinline__ CollideConst<float> early(const CollideConst<float>& 
                       "+s"(k.a_s), "+s"(k.a_F), "+s"(k.a_m), "+s"(k.w_tr), "+s"(k.c_tau),
                       "+s"(k.tau0), "+s"(k.rho0));
     return k;
+}
+__device__ __forceinline__ PlaneTable early(char* const* planes, char* (&held)[19]) {
+#pragma unroll
+    for (int i = 0; i < 19; ++i) held[i] = planes[i];
+    asm volatile("" : "+s"(held[0]), "+s"(held[1]), "+s"(held[2]), "+s"(held[3]), "+s"(held[4]),
+                      "+s"(held[5]), "+s"(held[6]), "+s"(held[7]), "+s"(held[8]), "+s"(held[9]));
+    asm volatile("" : "+s"(held[10]), "+s"(held[11]), "+s"(held[12]), "+s"(held[13]),
+                      "+s"(held[14]), "+s"(held[15]), "+s"(held[16]), "+s"(held[17]),
+                      "+s"(held[18]));
+    return PlaneTable{held};
 }
 __device__ __forceinline__ const CollideConst<double>& early(const CollideConst<double>& c) {
     return c;
@@ -265,6 +278,9 @@ __device__ __forceinline__ void step_cell(const LatticeArgs& L, uint32_t cell) {
         Fy *= s;
         Fz *= s;
     }
+    PlaneTable out{PAT == PAT_AB ? L.pb : L.pa};
+    char* held[19];
+    if constexpr (PAT == PAT_AB && std::is_same_v<Cd, CdF32>) out = early(L.pb, held);
     collide<R, kS>(g, Fx, Fy, Fz, k, inv_scale_of<R>(L));
     // Rebuild the store addresses from here: an empty register barrier on the
     // cell index keeps the compiler from holding 19 precomputed 64-bit store
@@ -272,8 +288,7 @@ __device__ __forceinline__ void step_cell(const LatticeArgs& L, uint32_t cell) {
     // scalar-base + 32-bit-offset form as the loads.
     uint32_t cs = cell;
     asm volatile("" : "+v"(cs));
-    store_cell<Cd, PAT, (NT & 2) != 0>(PlaneTable{PAT == PAT_AB ? L.pb : L.pa}, cs, nb, g,
-                                       kS ? R(1) : scale_of<R>(L));
+    store_cell<Cd, PAT, (NT & 2) != 0>(out, cs, nb, g, kS ? R(1) : scale_of<R>(L));
 }
 
 }  // namespace lbm

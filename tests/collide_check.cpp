@@ -13,10 +13,12 @@
 // momentum  3000 FP32 steps of a lattice with a mean flow, for several rates s_m: what
 //           a step adds is rounding, without a preferred sign; 1e-9 of the momentum per
 //           step (1/60 of a unit in the last place) is allowed to be one.
+// rho0      lattices of any reference density and relaxation time.
 #include <stdio.h>
 #include <stdlib.h>
 
 #include <cmath>
+#include <initializer_list>
 #include <vector>
 
 static inline float __builtin_amdgcn_rcpf(float x) { return 1.0f / x; }
@@ -31,15 +33,16 @@ struct Rates {
 };
 static const double kTau0 = 0.51, kC = 0.13;
 
-static CollideConst<double> constants(const Rates& r) {
+static CollideConst<double> constants(const Rates& r, double rho0 = 1.0, double tau0 = kTau0,
+                                      double C2 = kC * kC) {
     CollideConst<double> k{};
-    k.tau0 = kTau0;
-    k.c3 = 3.0 * kC * kC;
-    k.a_e = r.e / 38.0;
-    k.b9 = 0.5 / kTau0;
-    k.tau0_sq = kTau0 * kTau0;
+    k.tau0 = tau0;
+    k.c3 = 3.0 * C2;
+    k.a_e = r.e / (38.0 * rho0);
+    k.b9 = 0.5 / (tau0 * rho0);
+    k.tau0_sq = tau0 * tau0;
     k.s_e = r.e; k.s_eps = r.eps; k.s_q = r.q; k.s_pi = r.pi; k.s_m = r.m;
-    k.rho0 = 1.0;
+    k.rho0 = rho0;
     lbm::fill_collide_coefficients(k);
     return k;
 }
@@ -202,6 +205,41 @@ static int momentum(const Rates& r) {
     return bad;
 }
 
+// The collision of rho0 2^n and populations times 2^n is 2^n times that of rho0; the
+// factors of two round nowhere, those of the rescaled strain norm apart (three roundings
+// of tau_e - tau0 more, which is a tenth of tau_e at most here).
+template <typename R>
+static int scaled(const Rates& r, std::initializer_list<int> powers,
+                  CollideConst<R> (*constants_of)(const CollideConst<double>&)) {
+    const int n = 8;
+    const double unit = sizeof(R) == 4 ? 6e-8 : 1.2e-16;
+    const std::vector<double> f0 = flow(n, 0.01);
+    int bad = 0;
+    for (int p : powers) {
+        double worst = 0, most = 0;
+        const CollideConst<R> k0 = constants_of(constants(r, 1.0, kTau0, 4.0));
+        const CollideConst<R> k1 = constants_of(constants(r, ldexp(1.0, p), kTau0, 4.0));
+        std::vector<R> a(f0.begin(), f0.end()), b(a);
+        for (R& v : b) v = (R)ldexp((double)v, p);
+        run(a, n, 4, [&](R (&g)[19]) { lbm::collide<R>(g, R(0), R(0), R(0), k0); });
+        run(b, n, 4, [&](R (&g)[19]) { lbm::collide<R>(g, R(0), R(0), R(0), k1); });
+        for (size_t c = 0; c < a.size(); ++c) {
+            worst = fmax(worst, fabs(ldexp((double)b[c], -p) - a[c]));
+            most = fmax(most, fabs((double)a[c]));
+        }
+        printf("rho0 = 2^%d: %.2e of the populations off those of rho0 = 1\n", p, worst / most);
+        if (!(worst <= 4 * 3 * unit * most)) bad = 1;
+    }
+    // a tau0 whose square leaves FP32: the shear rows keep all but 1/tau0 of themselves
+    const CollideConst<R> k = constants_of(constants(r, 1.0, 1e22, 4.0));
+    std::vector<R> a(f0.begin(), f0.end());
+    run(a, n, 1, [&](R (&g)[19]) { lbm::collide<R>(g, R(0), R(0), R(0), k); });
+    for (R v : a)
+        if (!std::isfinite(v)) bad = 1;
+    return bad;
+}
+static CollideConst<double> unrounded(const CollideConst<double>& k) { return k; }
+
 int main(int argc, char** argv) {
     if (argc != 3) return 2;
     Rates r;
@@ -211,6 +249,9 @@ int main(int argc, char** argv) {
         case 's': return accuracy<float>(r, lbm::round_constants(k), 4);
         case 'd': return accuracy<double>(r, k, 16);
         case 'm': return momentum(r);
+        case 'r':
+            return scaled<float>(r, {-90, -70, -45, -20, 20, 40, 70, 100}, lbm::round_constants) |
+                   scaled<double>(r, {-700, -400, 400, 700}, unrounded);
     }
     return 2;
 }

@@ -38,3 +38,7 @@ def test_collision_rounds_like_a_few_stores(check, what, s_m):
 @pytest.mark.parametrize("s_m", [0.49, 1.2, 1.98])
 def test_single_precision_steps_keep_the_momentum(check, s_m):
     assert check("momentum", s_m) == 0
+
+
+def test_any_reference_density(check):
+    assert check("rho0", 1.98) == 0
