@@ -210,8 +210,17 @@ __device__ __forceinline__ R inv_scale_of(const LatticeArgs& L) {
     else return L.inv_sigma_f;
 }
 
-// Body force at (x, row) from the row coefficients and the x-harmonic table:
-// F = c0 + A1 sin(2 pi x/nx) + B1 cos(2 pi x/nx) + A2 sin(4 pi x/nx) + B2 cos(4 pi x/nx).
+// Body force at a cell from the 15 coefficients of its row and the four harmonics of its
+// x (s1, c1, s2, c2 = sin, cos of 2 pi x/nx and 4 pi x/nx):
+// F = c0 + A1 s1 + B1 c1 + A2 s2 + B2 c2, in the explicit fused multiply-adds that every
+// kernel that collides shares (see collide).
+template <typename R>
+__device__ __forceinline__ void force_sum(const R* rc, R s1, R c1, R s2, R c2, R& Fx, R& Fy,
+                                          R& Fz) {
+    Fx = mad(c2, rc[12], mad(s2, rc[9], mad(c1, rc[6], mad(s1, rc[3], rc[0]))));
+    Fy = mad(c2, rc[13], mad(s2, rc[10], mad(c1, rc[7], mad(s1, rc[4], rc[1]))));
+    Fz = mad(c2, rc[14], mad(s2, rc[11], mad(c1, rc[8], mad(s1, rc[5], rc[2]))));
+}
 template <typename R>
 __device__ __forceinline__ void force_at(const LatticeArgs& L, const CellPos& p, R& Fx, R& Fy,
                                          R& Fz) {
@@ -219,12 +228,8 @@ __device__ __forceinline__ void force_at(const LatticeArgs& L, const CellPos& p,
         Fx = Fy = Fz = R(0);
         return;
     }
-    const R* rc = (const R*)L.rowc + (uint64_t)p.row * 16;
     const R* xt = (const R*)L.xtab + (uint64_t)p.x * 4;
-    const R s1 = xt[0], c1 = xt[1], s2 = xt[2], c2 = xt[3];
-    Fx = rc[0] + s1 * rc[3] + c1 * rc[6] + s2 * rc[9] + c2 * rc[12];
-    Fy = rc[1] + s1 * rc[4] + c1 * rc[7] + s2 * rc[10] + c2 * rc[13];
-    Fz = rc[2] + s1 * rc[5] + c1 * rc[8] + s2 * rc[11] + c2 * rc[14];
+    force_sum((const R*)L.rowc + (uint64_t)p.row * 16, xt[0], xt[1], xt[2], xt[3], Fx, Fy, Fz);
 }
 
 // The collision's constants, read before the populations are waited for, and the planes

@@ -190,8 +190,7 @@ __global__ __launch_bounds__(Tb2Tile<kHaloWave>::kThreads) void k_step_tb2(TB2Ar
         if (z >= (int)L.nz) z -= (int)L.nz;
         return (uint32_t)z;
     };
-    // Force (eq. forcing_pattern via the row / x-harmonic tables): F = c0 + A1 s1 +
-    // B1 c1 + A2 s2 + B2 c2.  The x harmonics stay in registers; a row's coefficients
+    // Force (eq. forcing_pattern, force_sum).  The x harmonics stay in registers; a row's coefficients
     // are pulled by the row's own wave (one value a lane) with the populations of the
     // plane before, and go through LDS to the wave and the halo columns of that row.
     const bool forced = L.rowc != nullptr;
@@ -243,10 +242,7 @@ __global__ __launch_bounds__(Tb2Tile<kHaloWave>::kThreads) void k_step_tb2(TB2Ar
 #pragma unroll
             for (int i = 0; i < 19; ++i) g[i] = dec<Cd>(P.g[i], load_s);
             if (forced) {
-                const R* rc = rowbuf[uj & 1][ey];
-                Fx = rc[0] + h1 * rc[3] + h2 * rc[6] + h3 * rc[9] + h4 * rc[12];
-                Fy = rc[1] + h1 * rc[4] + h2 * rc[7] + h3 * rc[10] + h4 * rc[13];
-                Fz = rc[2] + h1 * rc[5] + h2 * rc[8] + h3 * rc[11] + h4 * rc[14];
+                force_sum<R>(rowbuf[uj & 1][ey], h1, h2, h3, h4, Fx, Fy, Fz);
                 if constexpr (k16) {
                     Fx *= s_st;
                     Fy *= s_st;
