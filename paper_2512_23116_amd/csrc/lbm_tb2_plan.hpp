@@ -22,6 +22,8 @@ struct Tb2Tile {
     static constexpr int EX = TX + 2, EY = TY + 2;
     static constexpr int kThreads = 64 * (EY + (kWave ? 1 : 0));
 };
+// The tile of make_plan where none is named: 64 x 13.  tiles_x, tiles_y and the tile have to
+// belong together; a launch names its own.
 constexpr int TB_TX = Tb2Tile<true>::TX, kTbTY = Tb2Tile<true>::TY;
 constexpr int TB_MAX_CHUNKS = 64;
 
