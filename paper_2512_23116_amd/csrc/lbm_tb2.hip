@@ -32,6 +32,7 @@
 #include <atomic>
 #include <map>
 #include <mutex>
+#include <utility>
 
 #include "lbm_device.hpp"
 #include "lbm_tb2_plan.hpp"
@@ -60,24 +61,20 @@ __device__ __forceinline__ uint32_t wrap_add(uint32_t base, int d, uint32_t n) {
 
 // What holds this kernel is the cache lines it moves, not its instructions: with the
 // loads and stores taken out it takes 1.7 of 6.1 ms (512^3 FP32), loads alone 3.2 and
-// stores alone 3.1, and their times add.  Hence the two tiles (Tb2Tile; launch_cd):
+// stores alone 3.1, and their times add.  Hence the two tiles (Tb2Tile):
 //   - kHaloWave: 64 x 13 columns, a wave per row of the extended tile, and the columns
 //     left and right of the rows in a wave of their own.  Where a lattice row is a whole
 //     number of 128-byte lines the tile's rows are whole lines too.  Row pieces of 62
 //     columns start anywhere, so that two of the three lines of every stored piece are
 //     written in parts by two workgroups.
 //   - 62 x 14 columns, 64 x 16 with the halo, a wave per row, where rows start anywhere
-//     in a line in any case: the halo columns cost no lines of their own.  In FP32 only
-//     where its last column of tiles is at most half full: with full ones throughout,
-//     neighbours lose the lines they share before the other has used them (the 4 MB of
-//     an XCD's L2 hold less than one plane of its 32 tiles) and it fetches 1.40 times
-//     what it needs at 308^3 against 1.24 at 331^3; 64 x 13 does not.
-//   ms per launch (two steps)      62 x 14    64 x 13    before both
-//     512^3 FP32                     4.9        4.3         6.1
-//     256^3 FP32 / FP16          0.67 / 0.51  0.62 / 0.48   0.84 / 0.60
-//     306^3, 370^3, 492^3 FP32   1.32 2.67 5.29  1.10 2.06 4.62  1.18 2.71 5.23
-//     260^3, 331^3, 450^3 FP32   0.72 1.32 3.61  0.78 1.53 3.84  0.80 1.56 3.92
-//     400^3 BF16, 800^3 FP16     1.94 12.2    2.10 14.4     2.27 13.8
+//     in a line in any case: the halo columns cost no lines of their own.
+// wide_tile says which lattice takes which, with both measured.  Before there were two,
+// the kernel took 6.1 ms at 512^3 FP32 (4.4 now), 0.83 / 0.56 at 256^3 FP32 / FP16 (0.61 /
+// 0.46), 2.26 at 400^3 BF16 (1.98), 14.0 at 800^3 FP16 (12.9).  Of 48 FP32 and 28 16-bit
+// lattices timed against that kernel, FP32 ones with rows of no whole 32-byte sectors are
+// slower in two places: 236^3 to 245^3 by 2 to 3 % (it fetches two planes ahead, and the
+// lines that neighbours share leave the L2 sooner), 470^3 and 475^3 by 3 to 5 %.
 // What a plane's pulls wait for matters next.  Loads and stores of a wave complete in
 // order under one counter, so nothing in the loop is loaded to be used at once (a
 // force-table load per plane, waited for, had drained every pull and store in flight),
@@ -190,9 +187,10 @@ __global__ __launch_bounds__(Tb2Tile<kHaloWave>::kThreads) void k_step_tb2(TB2Ar
         if (z >= (int)L.nz) z -= (int)L.nz;
         return (uint32_t)z;
     };
-    // Force (eq. forcing_pattern, force_sum).  The x harmonics stay in registers; a row's coefficients
-    // are pulled by the row's own wave (one value a lane) with the populations of the
-    // plane before, and go through LDS to the wave and the halo columns of that row.
+    // Force (eq. forcing_pattern, force_sum).  The x harmonics stay in registers; a row's
+    // coefficients are pulled by the row's own wave (one value a lane) with the
+    // populations of the plane before, and go through LDS to the wave and the halo
+    // columns of that row.
     const bool forced = L.rowc != nullptr;
     R h1 = R(0), h2 = R(0), h3 = R(0), h4 = R(0);
     if (forced) {
@@ -319,6 +317,12 @@ bool tb2_supported(int precision) { return precision != LBM_FP64; }
 
 namespace {
 
+// Tiles of a lattice along x and y.
+template <class Tile>
+std::pair<uint32_t, uint32_t> tiles_of(const LatticeArgs& L) {
+    return {(L.nx + Tile::TX - 1) / Tile::TX, (L.ny + Tile::TY - 1) / Tile::TY};
+}
+
 // Compute units of the current device, asked once per device.
 uint32_t compute_units() {
     static std::atomic<int> cus[64];
@@ -336,31 +340,29 @@ uint32_t compute_units() {
 
 // Plans are made once per (shape, grouping, CU count) and kept.
 template <class Tile>
-const Tb2Plan& plan_for(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t tiles_x,
-                        uint32_t tiles_y, uint32_t groups) {
+const Tb2Plan& plan_for(const LatticeArgs& L, uint32_t groups) {
     static std::mutex mu;
     static std::map<std::array<uint32_t, 5>, Tb2Plan> plans;
     const uint32_t cus = compute_units();
-    const std::array<uint32_t, 5> key{nx, ny, nz, groups, cus};
+    const std::array<uint32_t, 5> key{L.nx, L.ny, L.nz, groups, cus};
     std::lock_guard<std::mutex> lock(mu);
     auto it = plans.find(key);
     if (it == plans.end())
-        it = plans.emplace(key, make_plan(nx, ny, nz, tiles_x, tiles_y, groups, cus, Tile::TX, Tile::TY)).first;
+        it = plans.emplace(key, make_plan(L.nx, L.ny, L.nz, tiles_of<Tile>(L).first,
+                                          tiles_of<Tile>(L).second, groups, cus, Tile::TX,
+                                          Tile::TY)).first;
     return it->second;
 }
 
 }  // namespace
 
 template <class Cd, bool kHaloWave>
-static hipError_t launch_tile(const LatticeArgs& L, hipStream_t s) {
+static hipError_t launch_tile(const LatticeArgs& L, const Tb2Plan& P, hipStream_t s) {
     using Tile = Tb2Tile<kHaloWave>;
     TB2Args A;
     A.L = L;
-    A.tiles_x = (L.nx + Tile::TX - 1) / Tile::TX;
-    A.tiles_y = (L.ny + Tile::TY - 1) / Tile::TY;
-    // one tile range per XCD whenever a block order is asked for
-    const uint32_t groups = L.xcd_remap ? 8u : 1u;
-    const Tb2Plan& P = plan_for<Tile>(L.nx, L.ny, L.nz, A.tiles_x, A.tiles_y, groups);
+    A.tiles_x = tiles_of<Tile>(L).first;
+    A.tiles_y = tiles_of<Tile>(L).second;
     A.W = P.w;
     const uint64_t nblocks = (uint64_t)P.w.groups * P.per_group;
     if (nblocks == 0 || nblocks > 0x7fffffffull) return hipErrorInvalidValue;
@@ -371,15 +373,16 @@ static hipError_t launch_tile(const LatticeArgs& L, hipStream_t s) {
 
 template <class Cd>
 static hipError_t launch_cd(const LatticeArgs& L, hipStream_t s) {
-    // whole lines per lattice row (a plane starts on one): the tile that keeps to them;
-    // else 62 x 14, but in FP32 only if that leaves its last column of tiles at most half
-    // full (both sides of both lines measured at k_step_tb2)
-    using T = typename Cd::T;
-    using Wide = Tb2Tile<false>;
-    const bool whole_lines = (uint64_t)L.nx * sizeof(T) % 128 == 0;
-    const bool full = (L.nx - 1) % Wide::TX + 1 > Wide::TX / 2;
-    return whole_lines || (sizeof(T) == 4 && full) ? launch_tile<Cd, true>(L, s)
-                                                   : launch_tile<Cd, false>(L, s);
+    // one tile range per XCD whenever a block order is asked for
+    const uint32_t groups = L.xcd_remap ? 8u : 1u;
+    constexpr uint32_t bytes = sizeof(typename Cd::T);
+    const Tb2Plan& narrow = plan_for<Tb2Tile<false>>(L, groups);
+    if (wide_possible(L.nx, L.ny, bytes)) {
+        const Tb2Plan& wide = plan_for<Tb2Tile<true>>(L, groups);
+        if (wide_tile(L.nx, L.ny, bytes, wide.makespan, narrow.makespan))
+            return launch_tile<Cd, true>(L, wide, s);
+    }
+    return launch_tile<Cd, false>(L, narrow, s);
 }
 
 hipError_t launch_step_tb2(int precision, const LatticeArgs& L, hipStream_t s) {

@@ -56,6 +56,7 @@ __host__ __device__ inline bool tb2_item(const Tb2Work& W, uint32_t nz, uint32_t
 struct Tb2Plan {
     Tb2Work w{};
     uint32_t per_group = 0;   // workgroups per group: the launch has groups * per_group
+    double makespan = 0.0;    // estimated finishing time, in planes of a full tile
 };
 
 // Relative cost of one plane of a tile: phase 1 runs on all its columns,
@@ -136,6 +137,7 @@ inline Tb2Plan make_plan(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t tiles_x
         if (best_ms < 0.0 || ms < best_ms * (1.0 - 1e-9)) {
             best_ms = ms;
             best = P;
+            best.makespan = ms;
         }
     };
     consider(nz);                          // one chunk: always possible
@@ -146,6 +148,36 @@ inline Tb2Plan make_plan(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t tiles_x
         best.per_group = std::max(best.per_group, items);
     }
     return best;
+}
+
+// Which tile a lattice takes, 64 x 13 (true) or 62 x 14, from the finishing times that
+// their plans estimate.  ms per launch at n^3, 64 x 13 / 62 x 14:
+//  * Rows of whole 128-byte lines: 64 x 13, whose rows are whole lines too, unless its
+//    plan is the longer one (the last tile column or row mostly empty).
+//      FP32  256: 0.61/0.69  320: 1.09/1.30  512: 4.36/4.85;  288: 0.88/0.80  352: 2.12/1.62
+//      FP16  256: 0.46/0.51  512: 3.39/3.60;                  640: 7.02/6.44
+//    (plans of equal length go to 64 x 13: 96 0.041/0.046, but 160 0.202/0.189.)
+//  * Other rows, 16-bit: 62 x 14.  245: 0.48/0.38  331: 1.20/0.95  400: 2.05/1.89
+//  * Other rows, FP32, while a plane of the 19 populations fits the 4 MB L2 of an XCD,
+//    where tiles find the lines they share: 62 x 14.
+//      100: 0.047/0.044  112: 0.081/0.050  184: 0.32/0.27  232: 0.52/0.47
+//  * Past that 62 x 14 loses those lines where its last tile column is more than three
+//    quarters full (with a narrower one the neighbours keep step): 64 x 13 then, if its
+//    plan is not much the longer one, and wherever its plan is the shorter one.
+//      245: 0.63/0.68  306: 1.10/1.33  370: 2.10/2.69  434: 3.0/3.9  492: 4.9/5.4
+//      440: 3.04/3.35 (shorter plan);  248: 0.71/0.58 (plan 1.16 times as long)
+//      260: 0.80/0.75  331: 1.63/1.31  392: 2.59/2.22  450: 3.87/3.68  475: 4.7/4.6
+// (wide_possible: the plans need not be asked where it is false; at 800^3 one takes 18 ms.)
+inline bool wide_possible(uint32_t nx, uint32_t ny, uint32_t elem_bytes) {
+    return (uint64_t)nx * elem_bytes % 128 == 0 ||
+           (elem_bytes == 4 && (uint64_t)nx * ny * 19 * elem_bytes > (4u << 20));
+}
+inline bool wide_tile(uint32_t nx, uint32_t ny, uint32_t elem_bytes, double wide, double narrow) {
+    if (!wide_possible(nx, ny, elem_bytes)) return false;
+    if ((uint64_t)nx * elem_bytes % 128 == 0) return wide <= narrow;
+    const uint32_t tx = Tb2Tile<false>::TX;
+    const bool full = 4 * ((nx - 1) % tx + 1) > 3 * tx;
+    return wide < narrow || (full && wide < 1.12 * narrow);
 }
 
 }  // namespace lbm
