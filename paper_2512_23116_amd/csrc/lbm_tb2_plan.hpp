@@ -155,8 +155,9 @@ inline Tb2Plan make_plan(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t tiles_x
 //  * Rows of whole 128-byte lines: 64 x 13, whose rows are whole lines too, unless its
 //    plan is the longer one (the last tile column or row mostly empty).
 //      FP32  256: 0.61/0.69  320: 1.09/1.30  512: 4.36/4.85;  288: 0.88/0.80  352: 2.12/1.62
-//      FP16  256: 0.46/0.51  512: 3.39/3.60;                  640: 7.02/6.44
-//    (plans of equal length go to 64 x 13: 96 0.041/0.046, but 160 0.202/0.189.)
+//      FP16  256: 0.46/0.51  512: 3.39/3.60;  640: 7.1/6.5  704: 8.9/8.3
+//    In FP32 by 2 % (640: 9.3/9.9, 704: 12.2/13.8, of plans 1.006 and 1.004 times as long),
+//    or where 62 x 14 has a full last column (below; 608: 7.5/8.4, 800: 17.8/18.8).
 //  * Other rows, 16-bit: 62 x 14.  245: 0.48/0.38  331: 1.20/0.95  400: 2.05/1.89
 //  * Other rows, FP32, while a plane of the 19 populations fits the 4 MB L2 of an XCD,
 //    where tiles find the lines they share: 62 x 14.
@@ -174,10 +175,11 @@ inline bool wide_possible(uint32_t nx, uint32_t ny, uint32_t elem_bytes) {
 }
 inline bool wide_tile(uint32_t nx, uint32_t ny, uint32_t elem_bytes, double wide, double narrow) {
     if (!wide_possible(nx, ny, elem_bytes)) return false;
-    if ((uint64_t)nx * elem_bytes % 128 == 0) return wide <= narrow;
     const uint32_t tx = Tb2Tile<false>::TX;
+    const bool lines = (uint64_t)nx * elem_bytes % 128 == 0;
+    if (elem_bytes != 4) return wide <= narrow;
     const bool full = 4 * ((nx - 1) % tx + 1) > 3 * tx;
-    return wide < narrow || (full && wide < 1.12 * narrow);
+    return wide < (lines ? 1.02 : 1.0) * narrow || (full && wide < 1.12 * narrow);
 }
 
 }  // namespace lbm

@@ -94,10 +94,11 @@ static int choice() {
                           {306, 4, true},  {320, 4, true},  {331, 4, false}, {352, 4, false},
                           {360, 4, true},  {370, 4, true},  {384, 4, true},  {392, 4, false},
                           {420, 4, true},  {434, 4, true},  {440, 4, true},  {492, 4, true},
-                          {512, 4, true},  {64, 2, true},   {128, 2, true},  {184, 2, false},
+                          {512, 4, true},  {576, 4, true},  {608, 4, true},  {640, 4, true},
+                          {672, 4, true},  {704, 4, true},  {800, 4, true},  {64, 2, true},   {128, 2, true},  {184, 2, false},
                           {240, 2, false}, {256, 2, true},  {260, 2, false}, {320, 2, true},
                           {331, 2, false}, {384, 2, true},  {400, 2, false}, {450, 2, false},
-                          {512, 2, true},  {640, 2, false}};
+                          {512, 2, true},  {640, 2, false}, {704, 2, false}};
     for (const Case& c : cases) {
         using W = lbm::Tb2Tile<true>;
         using N = lbm::Tb2Tile<false>;
