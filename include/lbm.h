@@ -315,16 +315,20 @@ lbm_status lbm_spectrum(lbm_handle* h, int32_t kmax, double* E);
  * ratio does not equal 1 for isotropic fields; this is the isotropic relation
  * E_22 = (E_11 - k dE_11/dk) / 2, under which IC = 1.  FP64 FFT (hipFFT) on the
  * device, sums in a fixed order (bitwise the same on every call).  Host
- * double[9 (kmax+1)] and double[kmax+1].  Shares the analysis buffers and FFT
- * plan of lbm_spectrum.  Synchronises. */
+ * double[9 (kmax+1)] and double[kmax+1].  Shares the analysis buffers of
+ * lbm_spectrum, and its FFT plan except at exactly 2^24 cells, where this call
+ * transforms a component at a time; its partial sums, kept with them, take 24 KB
+ * per bin, or 72 KB while that is at most 16 MB.  Synchronises. */
 lbm_status lbm_spectra_1d(lbm_handle* h, int32_t kmax, double* E, double* ic);
 
 /* Longitudinal structure functions of the current state (Sec. 5.3): for each
  * separation rs[j] >= 1 (taken modulo the lattice size per axis),
  *   out[6 j + m] = mean over cells x and axes a of p_m(du),
  *   du = u_a(x + r e_a) - u_a(x) (periodic),  p = (du^2, du^3, |du|^3, du^4, |du|^5, du^6).
- * F4(r) = out[6j+3] / out[6j]^2.  FP64, reduced in a fixed order (bitwise
- * reproducible).  nr in 1..65535.  Uses the handle's analysis velocity buffer
+ * F4(r) = out[6j+3] / out[6j]^2.  FP64, reduced in an order that the lattice
+ * and the list of separations fix: the same call gives the same bits, but the
+ * last bits of one separation depend on how many others are asked for with it.
+ * nr in 1..65535.  Uses the handle's analysis velocity buffer
  * (created on first use, 24 bytes per cell) and under 1 MB of partial sums that
  * the handle keeps.  Synchronises. */
 lbm_status lbm_structure_functions(lbm_handle* h, const int32_t* rs, int32_t nr, double* out);

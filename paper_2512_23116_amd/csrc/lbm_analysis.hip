@@ -686,11 +686,14 @@ lbm_status lbm_spectra_1d(lbm_handle* h, int32_t kmax, double* E, double* ic) {
     AnalysisCache& a = cache(h);
     // one call for the three transforms and one for each sum over them (32^3 111 ->
     // 45 us, 128^3 222 -> 153, 240^3 885 -> 857); from 2^24 cells a component at a time,
-    // whose sums fold what is still in the cache (256^3 1110 us, batched 1130)
+    // whose sums fold what is still in the cache (256^3 1110 us, batched 1130).  The
+    // handle keeps the partial sums: past 16 MB for the three (kmax 226) the components'
+    // sums take turns in one component's
     const bool batched = h->args.ncell < (size_t(1) << 24);
-    const int passes = batched ? 1 : 3, ncomp = batched ? 3 : 1;
-    hipError_t e = ensure(a.c, a.c_elems, ncomp * nmodes);
-    if (e == hipSuccess) e = ensure(a.part, a.part_elems, (size_t)ncomp * kAnaBlocks * cols);
+    const size_t part = (size_t)kAnaBlocks * cols;
+    const int together = batched && 3 * part * sizeof(double) <= (size_t(16) << 20) ? 3 : 1;
+    hipError_t e = ensure(a.c, a.c_elems, (batched ? 3 : 1) * nmodes);
+    if (e == hipSuccess) e = ensure(a.part, a.part_elems, together * part);
     if (e == hipSuccess) e = ensure(a.out, a.out_elems, (size_t)3 * cols);
     if (e != hipSuccess) return hip_err(h, e, "hipMalloc(one-dimensional spectra)");
     st = batched ? fft_plan3(h, a, h->stream) : fft_plan(h, a, h->stream);
@@ -699,13 +702,16 @@ lbm_status lbm_spectra_1d(lbm_handle* h, int32_t kmax, double* E, double* ic) {
     const size_t hb = (size_t)cols * sizeof(double);
     const int bt = bin_threads(hb);
     hipfftResult fr = HIPFFT_SUCCESS;
-    for (int c = 0; c < passes && fr == HIPFFT_SUCCESS; ++c) {
-        fr = hipfftExecD2Z(batched ? a.plan3 : a.plan, (hipfftDoubleReal*)(u + (size_t)c * nc), a.c);
+    for (int c = 0; c < 3 && fr == HIPFFT_SUCCESS; c += together) {
+        if (!batched)
+            fr = hipfftExecD2Z(a.plan, (hipfftDoubleReal*)(u + (size_t)c * nc), a.c);
+        else if (c == 0)
+            fr = hipfftExecD2Z(a.plan3, (hipfftDoubleReal*)u, a.c);
         if (fr != HIPFFT_SUCCESS) break;
-        hipLaunchKernelGGL(k_axis_bin, dim3(kAnaBlocks, ncomp), dim3(bt), hb * (bt / 64), h->stream,
-                           (const hipfftDoubleComplex*)a.c, (uint64_t)nmodes, nx, ny, nz,
-                           (int)kmax, inv_n2, a.part);
-        hipLaunchKernelGGL(k_sum_rows, dim3(cols, ncomp), dim3(256), 0, h->stream,
+        hipLaunchKernelGGL(k_axis_bin, dim3(kAnaBlocks, together), dim3(bt), hb * (bt / 64), h->stream,
+                           (const hipfftDoubleComplex*)a.c + (batched ? c * nmodes : 0),
+                           (uint64_t)nmodes, nx, ny, nz, (int)kmax, inv_n2, a.part);
+        hipLaunchKernelGGL(k_sum_rows, dim3(cols, together), dim3(256), 0, h->stream,
                            (const double*)a.part, kAnaBlocks, cols, 1.0, 0,
                            a.out + (size_t)c * cols);
     }
