@@ -294,8 +294,7 @@ __attribute__((amdgpu_waves_per_eu(8, 8))) void k_structure(StructArgs A, double
 
 // The same sums for the separation r[blockIdx.y], each block a row of
 // partials[r][block]: a thread per cell reads its neighbours along the axes from memory.
-// For one separation, where reading the velocity once more than the tiles do costs less
-// than going through LDS (256^3: 0.12 ms against 0.17), and for lines too long for LDS.
+// For few separations (struct_direct), and for lines too long for LDS.
 __global__ __launch_bounds__(256) void k_structure_direct(StructArgs A, DivMagic mx, DivMagic my,
                                                           double* partials) {
     __shared__ double red[4][6];
@@ -354,6 +353,21 @@ static size_t struct_plan(StructArgs& A) {
         most = std::max(most, X.n * X.w);
     }
     return most * sizeof(double);
+}
+
+// Whether a launch of few separations reads the velocity from memory for each instead
+// of going through LDS: a first separation takes 8 to 38 us less that way, and each
+// further one adds its reads.  us per call at n^3, memory / LDS:
+//   32^3  16 separations: 40.5/42.0       64^3   4: 49/52   5: 52/48
+//   100^3  4: 69/70   5: 73/68            128^3  3: 86/89   4: 95/89
+//   160^3  2: 138/144  3: 160/148         200^3  1: 216/240  2: 256/241
+// Rows of at most 128 bytes fill the tiles of the other axes badly (nx = 4, ny = nz = 512,
+// 8 separations: 78/92; nx = 8, 4 separations: 95/109).
+static bool struct_direct(const StructArgs& A) {
+    const uint64_t cells = (uint64_t)A.nx * A.ny * A.nz;
+    if (A.nr == 1 || cells <= 40000) return true;
+    if (A.nx < 16) return A.nr <= (A.nx < 8 ? 8 : 5);
+    return A.nr <= 4 && (A.nr - 1) * cells <= 5000000;
 }
 
 }  // namespace lbm
@@ -776,7 +790,7 @@ lbm_status lbm_structure_functions(lbm_handle* h, const int32_t* rs, int32_t nr,
         A.share = kWaves / A.pairs;
         for (int k = 0; k < A.nr; ++k) A.r[k] = (uint32_t)rs[j + k];
         int rows;
-        if (tiled && A.nr > 1) {
+        if (tiled && !struct_direct(A)) {
             const int nb = (int)std::min<uint32_t>(kAnaBlocks, A.first[3]);
             rows = nb * A.share;
             hipLaunchKernelGGL(k_structure, dim3(nb), dim3(kStructThreads), shm, h->stream, A,
