@@ -70,7 +70,11 @@ struct CollideConst {
                  // 0 in the self-consistent mode
     R b9;        // s_9 / (2 rho0): coefficient of m9_neq in S_xx; s_9 = 1/tau0
                  // (explicit mode) or 1 (self-consistent mode: |S| = |S_1| / tau_e)
-    R s_e, s_eps, s_q, s_pi, s_m;
+};
+
+// The fixed relaxation rates.
+struct Rates {
+    double s_e, s_eps, s_q, s_pi, s_m;
 };
 
 // Result of the macroscopic / closure half of the collision.
@@ -82,21 +86,22 @@ struct CellMacro {
     R snorm2;  // |S|^2 = 2 S:S of the strain that sets tau_e (diagnostics only)
 };
 
-// The coefficients of collide from the rates already in k.  Every row of
+// The coefficients of collide from the rates and what k holds.  Every row of
 // eq. mrt_les_guo is m* = (1 - s) m + s m_eq + (1 - s/2) F_m, a linear form of the
 // pair sums and differences, the momentum, rho u u and u F; the rows with fixed
 // rates are folded here into one coefficient per input and output.
 // scale: the storage scale, in whose units collide's kScaled works.
-inline void fill_collide_coefficients(CollideConst<double>& k, double scale = 1.0) {
-    const double ge = 1.0 - 0.5 * k.s_e, geps = 1.0 - 0.5 * k.s_eps;
+inline void fill_collide_coefficients(CollideConst<double>& k, const Rates& rates,
+                                      double scale = 1.0) {
+    const double ge = 1.0 - 0.5 * rates.s_e, geps = 1.0 - 0.5 * rates.s_eps;
     // t1 = m1*/2394, t2 = m2*/252 as forms of (sa, sd, r, rho u^2, u.F), with
     // m1 = -11 sa + 8 sd - 30 r, m2 = -4 sa + sd + 12 r, t0 = (sa + sd + r)/19
     const double t0 = 1.0 / 19.0;
-    const double t1[5] = {-11.0 / 2394.0, (8.0 - 19.0 * k.s_e) / 2394.0,
-                          (-30.0 + 19.0 * k.s_e) / 2394.0, 19.0 * k.s_e / 2394.0,
+    const double t1[5] = {-11.0 / 2394.0, (8.0 - 19.0 * rates.s_e) / 2394.0,
+                          (-30.0 + 19.0 * rates.s_e) / 2394.0, 19.0 * rates.s_e / 2394.0,
                           38.0 * ge / 2394.0};
-    const double e2 = (1.0 - k.s_eps) / 252.0;
-    const double t2[5] = {-4.0 * e2, e2, 12.0 * e2, -475.0 / 63.0 * k.s_eps / 252.0,
+    const double e2 = (1.0 - rates.s_eps) / 252.0;
+    const double t2[5] = {-4.0 * e2, e2, 12.0 * e2, -475.0 / 63.0 * rates.s_eps / 252.0,
                           -11.0 * geps / 252.0};
     double* ea[5] = {&k.ea_sa, &k.ea_sd, &k.ea_r, &k.ea_u2, &k.ea_uF};
     double* ed[5] = {&k.ed_sa, &k.ed_sd, &k.ed_r, &k.ed_u2, &k.ed_uF};
@@ -105,16 +110,16 @@ inline void fill_collide_coefficients(CollideConst<double>& k, double scale = 1.
         *ea[i] = m - 11.0 * t1[i] - 4.0 * t2[i];
         *ed[i] = m + 8.0 * t1[i] + t2[i];
     }
-    k.pi_m = 1.0 - k.s_pi;
-    k.pi_F = -(1.0 - 0.5 * k.s_pi);
+    k.pi_m = 1.0 - rates.s_pi;
+    k.pi_F = -(1.0 - 0.5 * rates.s_pi);
     // odd rows: j* = rho u + F/2 and q* of rows 4, 6, 8 in terms of d0,
     // s0 = rho u_x - 3 d0 and F_x per axis; rows 16..18 as they are
-    const double q = k.s_q;
+    const double q = rates.s_q;
     k.o_s = q / 6.0;
     k.o_F = (2.0 - q) / 12.0;
     k.a_s = (3.0 - q) / 24.0;
     k.a_F = (1.0 + q) / 48.0;
-    k.a_m = (1.0 - k.s_m) / 8.0;
+    k.a_m = (1.0 - rates.s_m) / 8.0;
     // |S|^2 = 6 (a_e n1)^2 + b9^2 (3 n9^2 + 9 n11^2 + 36 (n13^2 + n14^2 + n15^2)),
     // n1 = 19 (sd - r - rho u^2)
     k.w_tr = 2.0 * (19.0 * k.a_e / k.b9) * (19.0 * k.a_e / k.b9);
@@ -160,8 +165,7 @@ inline void round_even(double a, double d, float* fa, float* fd) {
 inline CollideConst<float> round_constants(const CollideConst<double>& k) {
     CollideConst<float> f{};
     f.tau0 = (float)k.tau0; f.c3 = (float)k.c3; f.a_e = (float)k.a_e; f.b9 = (float)k.b9;
-    f.s_e = (float)k.s_e; f.s_eps = (float)k.s_eps; f.s_q = (float)k.s_q;
-    f.s_pi = (float)k.s_pi; f.s_m = (float)k.s_m; f.rho0 = (float)k.rho0;
+    f.rho0 = (float)k.rho0;
     f.tau0_sq = (float)k.tau0_sq; f.closure = k.closure;
     round_even(k.ea_sa, k.ed_sa, &f.ea_sa, &f.ed_sa);
     round_even(k.ea_sd, k.ed_sd, &f.ea_sd, &f.ed_sd);
@@ -261,9 +265,11 @@ __device__ __forceinline__ double scale2(double a, int e) { return __builtin_lde
 // Collide one cell in place (eq. mrt_les_guo).  g: deviation populations
 // (pre-collision in, post-collision out).  F: body force at the cell.
 //
-// The two-step and the 16-bit kernels are bound by VALU issue (and the rest run
-// with 25-36 % of it busy), so the moments are never formed one by one: rows with
-// a fixed rate are linear forms whose coefficients the host folds
+// The step kernels are bound by the cache lines they move, but the instructions of the
+// collision add to that where loads and stores are waited for (the VALUs are busy 22-29 %
+// of the time in the one-step FP32 kernels, 40 % in the two-step one and 48-61 % with
+// 16-bit storage), so the moments are never formed one by one: rows with a fixed rate are
+// linear forms whose coefficients the host folds
 // (fill_collide_coefficients), and only the five shear rows, whose rate differs
 // per cell, are relaxed as moments.  With A = p3 + p4, B = p5 + p6, C = p7 + p8:
 //   axis pairs, even:     ea +- ..., ea = forms of (sa, sd, r, rho u^2, u.F)

@@ -379,10 +379,9 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_handle** out) {
     kd.b9 = (sc ? 1.0 : 1.0 / cfg->tau0) / (2.0 * cfg->rho0);
     kd.tau0_sq = cfg->tau0 * cfg->tau0;
     kd.closure = sc ? kSelfConsistent : 0;
-    kd.s_e = cfg->s_e; kd.s_eps = cfg->s_eps; kd.s_q = cfg->s_q; kd.s_pi = cfg->s_pi;
-    kd.s_m = cfg->s_m;
     kd.rho0 = cfg->rho0;
-    fill_collide_coefficients(kd, h->cfg.storage_scale);
+    fill_collide_coefficients(kd, Rates{cfg->s_e, cfg->s_eps, cfg->s_q, cfg->s_pi, cfg->s_m},
+                              h->cfg.storage_scale);
     a.kf = round_constants(kd);
     a.tau0 = cfg->tau0;
     a.rho0 = cfg->rho0;

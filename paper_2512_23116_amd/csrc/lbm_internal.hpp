@@ -35,7 +35,7 @@ struct LatticeArgs {
     const void* xtab;        // [nx][4] sin/cos of the first two x harmonics, in R
     float sigma_f, inv_sigma_f;   // FP16/BF16 storage scale
     CollideConst<float> kf;  // collision constants, rounded to FP32 on the host
-    char* pa[19];            // plane i of a: a + i * plane * element bytes
+    alignas(64) char* pa[19];   // plane i of a: a + i * plane * element bytes
     char* pb[19];            // plane i of b (precomputed on the host: kernels take the
                              // 64-bit plane bases from kernel arguments, no scalar math)
     void* a;                 // population array (AA: the only one; AB: current source)

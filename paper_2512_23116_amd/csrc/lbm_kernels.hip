@@ -19,9 +19,13 @@
 namespace lbm {
 
 // ------------------------------------------------------------ the step ---
-// FP64 takes 96-104 VGPRs; held to 4 waves per SIMD, as its 108-114 had been, it runs
-// at 968 us on 256^3 A/B against 981 with the 5 that 96 allow (more waves than its
-// 8-byte streams gain from).  The rest run 8.
+// FP64 takes 92-98 VGPRs and is held to 4 waves per SIMD.  With the 5 that they allow
+// A/B takes 983 us at 256^3 and 1900 at 320^3 instead of 974 and 1870 (more waves than its
+// 8-byte streams gain from); AA and the sizes between differ by less than 0.5 %, and
+// lattices that fill the chip only once lose (32^3 A/B 4.2 against 4.1, 64^3 13.5 / 13.3).
+// The FP32 A/B step runs 7 waves, for the 106 scalars that both plane tables and the
+// collision's constants take (see early: 23.7 us at 100^3, 23.95 with 8 waves and the
+// tables loaded late), k_batch_step 7 too; the rest run 8.
 template <class Cd, int PAT, int NT>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(std::is_same_v<Cd, CdF64> ? 4 : 1,

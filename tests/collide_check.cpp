@@ -41,9 +41,8 @@ static CollideConst<double> constants(const Rates& r, double rho0 = 1.0, double 
     k.a_e = r.e / (38.0 * rho0);
     k.b9 = 0.5 / (tau0 * rho0);
     k.tau0_sq = tau0 * tau0;
-    k.s_e = r.e; k.s_eps = r.eps; k.s_q = r.q; k.s_pi = r.pi; k.s_m = r.m;
     k.rho0 = rho0;
-    lbm::fill_collide_coefficients(k);
+    lbm::fill_collide_coefficients(k, lbm::Rates{r.e, r.eps, r.q, r.pi, r.m});
     return k;
 }
 
