@@ -205,7 +205,8 @@ __device__ __forceinline__ void struct_sums(double (&acc)[6], double du) {
 // Sums of du^2, du^3, |du|^3, du^4, |du|^5, du^6 for each separation over the three
 // axes, du = u_a(x + r e_a) - u_a(x), periodic: one row of 6 per wave that shares a
 // separation, partials[r][block][share].  Bound by the FP64 unit (9 instructions per
-// axis, cell and separation) and, next, by LDS (1.5 reads).  256^3 with 14
+// axis, cell and separation) and, next, by LDS (1.5 reads).  Held to 8 waves, at the price
+// of two spilled registers (with 6 the call took 823 us where this took 764).  256^3 with 14
 // separations: 0.45 ms, of which 0.12 load the tiles; a thread per cell that read
 // u[x + r] from memory for every separation took 1.27.
 __global__ __launch_bounds__(kStructThreads)
