@@ -11,6 +11,7 @@
 // alone enters the odd-parity rows (3..8, 16..18).
 #pragma once
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -126,14 +127,16 @@ inline void fill_collide_coefficients(CollideConst<double>& k, const Rates& rate
     k.c_tau = k.c3 * k.b9 * 1.7320508075688772;
     // w is of the order of (rho0 scale)^2, its trace part of tau0^2 times that: out of
     // FP32 from rho0 = 2^64 or tau0 = 2^64 up, and at rho0 = 2^-43 a strain of 1e-6 is
-    // lost.  Well before that it is formed of moments divided by a power of two.
+    // lost.  Well before that it is formed of moments divided by a power of two.  (Where
+    // w_tr ends at the type's largest value, tau0 is so large that the shear is kept whole
+    // whatever w is, as long as it is a number.)
     int e, et;
     frexp(k.tau0, &et);
     frexp(k.rho0 * scale, &e);
     if (e > 32 || e < -16 || et > 20) {
         e += et > 0 ? et : 0;
         k.closure |= kRescaled | e * (1 << kScaleShift);
-        k.w_tr = sqrt(k.w_tr);
+        k.w_tr = fmin(1.4142135623730951 * 19.0 * k.a_e / k.b9, DBL_MAX);
         k.c_tau = ldexp(k.c_tau, e) / scale;
     }
 }
@@ -175,7 +178,7 @@ inline CollideConst<float> round_constants(const CollideConst<double>& k) {
     f.pi_m = (float)k.pi_m; f.pi_F = (float)k.pi_F;
     f.o_s = (float)k.o_s; f.o_F = (float)k.o_F;
     f.a_s = (float)k.a_s; f.a_F = (float)k.a_F; f.a_m = (float)k.a_m;
-    f.w_tr = (float)k.w_tr; f.c_tau = (float)k.c_tau;
+    f.w_tr = (float)fmin(k.w_tr, FLT_MAX); f.c_tau = (float)k.c_tau;
     return f;
 }
 

@@ -229,12 +229,18 @@ static int scaled(const Rates& r, std::initializer_list<int> powers,
         printf("rho0 = 2^%d: %.2e of the populations off those of rho0 = 1\n", p, worst / most);
         if (!(worst <= 4 * 3 * unit * most)) bad = 1;
     }
-    // a tau0 whose square leaves FP32: the shear rows keep all but 1/tau0 of themselves
-    const CollideConst<R> k = constants_of(constants(r, 1.0, 1e22, 4.0));
-    std::vector<R> a(f0.begin(), f0.end());
-    run(a, n, 1, [&](R (&g)[19]) { lbm::collide<R>(g, R(0), R(0), R(0), k); });
-    for (R v : a)
-        if (!std::isfinite(v)) bad = 1;
+    // a tau0 whose square leaves the type: the shear rows keep all but 1/tau0 of themselves
+    for (double tau0 : {1e22, 1e37, sizeof(R) == 4 ? 3e38 : 1e300}) {
+        const CollideConst<R> k = constants_of(constants(r, 1.0, tau0, 4.0));
+        std::vector<R> a(f0.begin(), f0.end()), b(f0.size(), R(0));
+        run(a, n, 2, [&](R (&g)[19]) { lbm::collide<R>(g, R(0), R(0), R(0), k); });
+        run(b, n, 2, [&](R (&g)[19]) { lbm::collide<R>(g, R(0), R(0), R(0), k); });   // at rest
+        for (R v : a)
+            if (!std::isfinite(v)) bad = 1;
+        for (R v : b)
+            if (v != 0) bad = 1;
+        if (bad) printf("tau0 = %g\n", tau0);
+    }
     return bad;
 }
 static CollideConst<double> unrounded(const CollideConst<double>& k) { return k; }
