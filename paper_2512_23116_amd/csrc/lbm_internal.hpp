@@ -35,7 +35,10 @@ struct LatticeArgs {
     const void* xtab;        // [nx][4] sin/cos of the first two x harmonics, in R
     float sigma_f, inv_sigma_f;   // FP16/BF16 storage scale
     CollideConst<float> kf;  // collision constants, rounded to FP32 on the host
-    alignas(64) char* pa[19];   // plane i of a: a + i * plane * element bytes
+    uint32_t pad_[5];        // the plane tables start a line (alignas would align the slots of
+                             // a batch table as well, and k_batch_step then takes 1 % more,
+                             // 3 % on the smallest batches)
+    char* pa[19];            // plane i of a: a + i * plane * element bytes
     char* pb[19];            // plane i of b (precomputed on the host: kernels take the
                              // 64-bit plane bases from kernel arguments, no scalar math)
     void* a;                 // population array (AA: the only one; AB: current source)
@@ -47,7 +50,8 @@ struct LatticeArgs {
     int32_t nt_mode;         // step kernel: bit 1 non-temporal stores
     uint32_t elem_bytes;     // bytes per stored population
 };
-static_assert(offsetof(LatticeArgs, kf) == 64 && offsetof(CollideConst<float>, c3) <= 96,
+static_assert(offsetof(LatticeArgs, kf) == 64 && offsetof(LatticeArgs, pa) == 192 &&
+                  offsetof(CollideConst<float>, c3) <= 96,
               "step arguments fit their cache lines");
 
 // Kernel launchers (lbm_kernels.hip).  All return the launch status.
