@@ -269,8 +269,8 @@ __device__ __forceinline__ double scale2(double a, int e) { return __builtin_lde
 // (pre-collision in, post-collision out).  F: body force at the cell.
 //
 // The step kernels are bound by the cache lines they move, but the instructions of the
-// collision add to that where loads and stores are waited for (the VALUs are busy 23-28 %
-// of the time in the one-step FP32 kernels, 39 % in the two-step one and 55-62 % with
+// collision add to that where loads and stores are waited for (the VALUs are busy 23-29 %
+// of the time in the one-step FP32 kernels, 39-44 % in the two-step one and 51-64 % with
 // 16-bit storage), so the moments are never formed one by one: rows with a fixed rate are
 // linear forms whose coefficients the host folds
 // (fill_collide_coefficients), and only the five shear rows, whose rate differs
